@@ -46,8 +46,9 @@
  *   are equal.  Scores are ranked exactly as given: no gating is applied.
  * - Limits: 1 <= E <= 1024, 1 <= k <= E, 1 <= N < 2^32, 1 <= L <= 65535 and
  *   E*(E-1)*N^2 < 2^64 (so the sum of squares is exact in 64 bits).
- *   The fast path needs 16-byte aligned scores with E*sizeof(score) a multiple
- *   of 16, E <= 256 and k <= 8; other valid shapes take a slower exact path.
+ *   The fast path takes rows of at least 16 bytes with E <= 256 and k <= 8
+ *   (fastest when the scores are 16-byte aligned and E*sizeof(score) is a
+ *   multiple of 128); other valid shapes take a slower exact path.
  */
 #ifndef DOLOSS_H
 #define DOLOSS_H

@@ -100,8 +100,9 @@ struct ProfEv {
 };
 
 // Top-K signatures of `nseg` segments; with a.cacc also the co-occurrence
-// counts of each segment's tokens added into a.cacc.  `pe` times the launch.
-hipError_t launch_topk(do_dtype dt, SegTable& tab, int nseg, const PathArgs& a, bool fast_ok, hipStream_t s,
+// counts of each segment's tokens added into a.cacc.  vec_rows: every score
+// row is 16-byte aligned.  `pe` times the launch.
+hipError_t launch_topk(do_dtype dt, SegTable& tab, int nseg, const PathArgs& a, bool vec_rows, hipStream_t s,
                        const ProfEv& pe = ProfEv{});
 
 // Co-occurrence counts of existing signatures: cacc[l][i][j] += popcount(F_i & F_j), i <= j,
