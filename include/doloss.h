@@ -48,7 +48,8 @@
  *   E*(E-1)*N^2 < 2^64 (so the sum of squares is exact in 64 bits).
  *   The fast path takes rows of at least 16 bytes with E <= 256 and k <= 8
  *   (fastest when the scores are 16-byte aligned and E*sizeof(score) is a
- *   multiple of 128); other valid shapes take a slower exact path.
+ *   multiple of 128), and 256 < E <= 1024 with k <= 16; other valid shapes
+ *   take a slower exact path.
  */
 #ifndef DOLOSS_H
 #define DOLOSS_H

@@ -127,6 +127,13 @@ do_status run_layers(const void* scores, do_dtype dt, int64_t N, int32_t E, int3
   return DO_OK;
 }
 
+// Co-occurrence counts of stored signatures added into cacc (do_set_option
+// chooses the popcount kernel for comparison).
+hipError_t run_gram(const u64* bits, int64_t W, int64_t ld, int32_t E, int32_t L, uint32_t* cacc, hipStream_t s) {
+  return dol::gram_mfma_enabled() ? dol::launch_gram_mfma(bits, W, ld, E, L, cacc, s)
+                                  : dol::launch_gram_bits(bits, W, ld, E, L, cacc, s);
+}
+
 }  // namespace
 
 // ---------------------------------------------------------------------------
@@ -251,13 +258,9 @@ DOLOSS_API do_status do_pairwise_hamming(const uint64_t* bits, int64_t N, int32_
   if (bits == nullptr || !aligned(bits, 8)) return fail(DO_ERR_INVALID_ARG, "bits is NULL or not 8-byte aligned");
   if (D == nullptr || !aligned(D, 4)) return fail(DO_ERR_INVALID_ARG, "D is NULL or not 4-byte aligned");
   const int64_t W = (N + 63) / 64;
-  DO_TRY(hip_status(dol::launch_fill_u32(D, (int64_t)L * E * E, 0u, stream), "fill"));
-  if (E <= dol::kFastMaxE && dol::gram_mfma_enabled())
-    DO_TRY(hip_status(dol::launch_gram_mfma(reinterpret_cast<const u64*>(bits), W, E, L, D, stream), "gram"));
-  else
-    DO_TRY(hip_status(
-        dol::launch_gram_bits(reinterpret_cast<const u64*>(bits), W, dol::sig_words(W), E, L, D, stream), "gram"));
-  return hip_status(dol::launch_finalize(D, D, nullptr, E, L, stream), "finalize");
+  DO_TRY(hip_status(dol::launch_clear(D, nullptr, E, L, stream), "fill"));
+  DO_TRY(hip_status(run_gram(reinterpret_cast<const u64*>(bits), W, dol::sig_words(W), E, L, D, stream), "gram"));
+  return hip_status(dol::launch_finalize(D, nullptr, E, L, stream), "finalize");
 }
 
 DOLOSS_API do_status do_loss(const uint32_t* D, int32_t E, int32_t L, do_loss_result* out, hipStream_t stream) {
@@ -279,16 +282,15 @@ DOLOSS_API do_status do_fused(const void* scores, do_dtype dtype, int64_t N, int
   if (E > dol::kFastMaxE && bits == nullptr)
     return fail(DO_ERR_INVALID_ARG, "do_fused needs a bits buffer when E > 256");
   DO_TRY(check_finite(&scores, 1, N * E * L, dtype, stream));
-  DO_TRY(hip_status(dol::launch_fill_u32(D, (int64_t)L * E * E, 0u, stream), "fill"));
+  DO_TRY(hip_status(dol::launch_clear(D, out, E, L, stream), "fill"));
   if (E <= dol::kFastMaxE) {
     DO_TRY(run_layers(scores, dtype, N, E, k, L, reinterpret_cast<u64*>(bits), D, stream));
   } else {
     DO_TRY(run_layers(scores, dtype, N, E, k, L, reinterpret_cast<u64*>(bits), nullptr, stream));
     const int64_t W = (N + 63) / 64;
-    DO_TRY(hip_status(
-        dol::launch_gram_bits(reinterpret_cast<const u64*>(bits), W, dol::sig_words(W), E, L, D, stream), "gram"));
+    DO_TRY(hip_status(run_gram(reinterpret_cast<const u64*>(bits), W, dol::sig_words(W), E, L, D, stream), "gram"));
   }
-  return hip_status(dol::launch_finalize(D, D, out, E, L, stream), "finalize");
+  return hip_status(dol::launch_finalize(D, out, E, L, stream), "finalize");
 }
 
 DOLOSS_API do_status do_surrogate(const void* p, do_dtype dtype, int64_t N, int32_t E, int32_t k, int32_t L,
@@ -558,9 +560,10 @@ DOLOSS_API do_status do_stream_finalize(do_stream* h, uint32_t* D, do_loss_resul
     return DO_OK;
   }
   // wider E: the Gram of the words holding this epoch's tokens
-  DO_TRY(hip_status(dol::launch_fill_u32(D, (int64_t)h->E * h->E, 0u, stream), "fill"));
-  DO_TRY(hip_status(dol::launch_gram_bits(h->hist, (h->tokens + 63) / 64, h->W, h->E, 1, D, stream), "gram"));
-  return hip_status(dol::launch_finalize(D, D, out, h->E, 1, stream), "finalize");
+  DO_TRY(hip_status(dol::launch_clear(D, out, h->E, 1, stream), "fill"));
+  if (h->tokens > 0)
+    DO_TRY(hip_status(run_gram(h->hist, (h->tokens + 63) / 64, h->W, h->E, 1, D, stream), "gram"));
+  return hip_status(dol::launch_finalize(D, out, h->E, 1, stream), "finalize");
 }
 
 DOLOSS_API do_status do_stream_reset(do_stream* h, hipStream_t stream) {

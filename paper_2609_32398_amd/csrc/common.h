@@ -110,18 +110,23 @@ hipError_t launch_topk(do_dtype dt, SegTable& tab, int nseg, const PathArgs& a, 
 // multiple of 8), layers E * ld words apart (signature layout: sig_off).
 hipError_t launch_gram_bits(const u64* bits, int64_t W, int64_t ld, int32_t E, int32_t L, uint32_t* cacc,
                             hipStream_t s);
-// The same Gram on fp4 MFMA tiles (E <= 256): counts added into cacc [L][E][E]
-// (upper triangle, zeroed by the caller); layers E * sig_words(W) words apart.
-hipError_t launch_gram_mfma(const u64* bits, int64_t W, int32_t E, int32_t L, uint32_t* cacc, hipStream_t s);
+// The same Gram on fp4 MFMA tiles: counts added into cacc [L][E][E] (upper
+// triangle, zeroed by the caller); ld = sig_words(W) for E <= 256.
+hipError_t launch_gram_mfma(const u64* bits, int64_t W, int64_t ld, int32_t E, int32_t L, uint32_t* cacc,
+                            hipStream_t s);
 // False when do_set_option selects the popcount Gram (a comparison switch).
 bool gram_mfma_enabled();
 // do_set_option: false for an unknown option or a value out of range.
 bool set_option(int opt, int value);
 
-// D = c_ii + c_jj - 2 c_ij (symmetric, zero diagonal); out (nullable) = loss.
-// cacc may alias D.
-hipError_t launch_finalize(const uint32_t* cacc, uint32_t* D, do_loss_result* out, int32_t E, int32_t L,
-                           hipStream_t s);
+// Zeroes the accumulators D [L][E][E] and, when out is given, the records that
+// launch_finalize accumulates into.
+hipError_t launch_clear(uint32_t* D, do_loss_result* out, int32_t E, int32_t L, hipStream_t s);
+
+// D holds the co-occurrence counts (upper triangle) and becomes
+// c_ii + c_jj - 2 c_ij (symmetric, zero diagonal); out (nullable, zeroed by
+// launch_clear) = loss.
+hipError_t launch_finalize(uint32_t* D, do_loss_result* out, int32_t E, int32_t L, hipStream_t s);
 
 // Surrogate loss (Eq. 7) and its gradient; a.loss must be zero.
 hipError_t launch_surrogate(do_dtype dt, const SurrogateArgs& a, hipStream_t s);

@@ -247,6 +247,10 @@ __device__ void block_sum2(u64& s1, u64& s2) {
   }
 }
 
+// Widest matrix that k_finalize (one block per layer, one launch) takes; wider
+// ones are split over rows (two launches).
+constexpr int kOneBlockE = 128;
+
 constexpr int kFinRows = 8;  // rows a wave reads before it writes (loads in flight per lane)
 constexpr int kFinCols = 2;  // 64-column blocks k_finalize reads together
 
@@ -304,6 +308,91 @@ __global__ __launch_bounds__(1024) void k_finalize(const uint32_t* cacc, uint32_
 }
 
 constexpr int kSplitRows = 8;  // rows per block of the split finalize, one per wave
+
+// The finalize of wide matrices over ceil(E/8) blocks per layer: one block per
+// layer took 27 us at 256 experts and 105 us at 512, most of the GPU idle; the
+// two kernels of this form take 5.8 + 1.8 to 4.8 us at either.  At 128 experts
+// one block takes 7 us and a second launch would eat the gain.
+// Wave w of block b owns row 8b + w.  The diagonal counts stay in place (every
+// block reads them; k_finalize_close zeroes them), and the exact sums go into
+// the layer's record with one atomic pair per block.  The mirrored entries are
+// transposed through LDS, so that column j receives its 8 values as 32
+// contiguous bytes instead of 8 strided stores.
+__global__ __launch_bounds__(512) void k_finalize_rows(uint32_t* d_all, do_loss_result* out, int E) {
+  extern __shared__ uint32_t sm[];
+  typedef uint32_t v4w __attribute__((ext_vector_type(4), aligned(4)));
+  uint32_t* diag = sm;       // [E]
+  uint32_t* vt = sm + E;     // [kSplitRows][E]
+  uint32_t* d = d_all + (int64_t)blockIdx.y * E * E;
+  for (int i = threadIdx.x; i < E; i += blockDim.x) diag[i] = d[(uint32_t)(i * E + i)];
+  __syncthreads();
+  const int w = (int)(threadIdx.x >> 6), lane = (int)(threadIdx.x & 63);
+  const int i0 = (int)blockIdx.x * kSplitRows, i = i0 + w;
+  u64 s1 = 0, s2 = 0;
+  if (i < E) {
+    const uint32_t row = (uint32_t)(i * E);
+    const uint32_t di = diag[i];
+    for (int jb = (i + 1) & ~63; jb < E; jb += 64 * 4) {
+      uint32_t cv[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int j = jb + 64 * q + lane;
+        cv[q] = d[j > i && j < E ? row + j : row];
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int j = jb + 64 * q + lane;
+        if (j > i && j < E) {
+          const uint32_t v = di + diag[j] - 2u * cv[q];
+          d[row + j] = v;
+          vt[w * E + j] = v;
+          s1 += 2ull * v;
+          s2 += 2ull * (u64)v * (u64)v;
+        }
+      }
+    }
+  }
+  __syncthreads();
+  for (int j = i0 + 1 + (int)threadIdx.x; j < E; j += blockDim.x) {
+    uint32_t* dst = d + (uint32_t)(j * E + i0);
+    if (j >= i0 + kSplitRows) {
+      uint32_t v[kSplitRows];
+#pragma unroll
+      for (int r = 0; r < kSplitRows; ++r) v[r] = vt[r * E + j];
+      *reinterpret_cast<v4w*>(dst) = v4w{v[0], v[1], v[2], v[3]};
+      *reinterpret_cast<v4w*>(dst + 4) = v4w{v[4], v[5], v[6], v[7]};
+    } else {
+      for (int r = 0; i0 + r < j; ++r) dst[r] = vt[r * E + j];
+    }
+  }
+  if (out == nullptr) return;
+  block_sum2(s1, s2);
+  if (threadIdx.x == 0) {
+    atomicAdd(reinterpret_cast<u64*>(&out[blockIdx.y].sum), s1);
+    atomicAdd(reinterpret_cast<u64*>(&out[blockIdx.y].sumsq), s2);
+  }
+}
+
+// After k_finalize_rows: the zero diagonal and the record from its sums.
+__global__ __launch_bounds__(256) void k_finalize_close(uint32_t* d, do_loss_result* out, int E) {
+  d += (int64_t)blockIdx.x * E * E;
+  for (int i = threadIdx.x; i < E; i += blockDim.x) d[(uint32_t)(i * E + i)] = 0u;
+  if (out != nullptr && threadIdx.x == 0) {
+    do_loss_result* o = out + blockIdx.x;
+    write_result(o, o->sum, 0ull, o->sumsq, E);
+  }
+}
+
+// Zeroes the accumulators and the records (nullable) of L layers: 16 bytes per
+// thread and pass (D is 4-byte aligned only).
+__global__ void k_clear(uint32_t* D, int64_t n, u64* rec, int64_t nrec) {
+  typedef uint32_t v4w __attribute__((ext_vector_type(4), aligned(4)));
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  for (int64_t i = i0; i < (n >> 2); i += stride) *reinterpret_cast<v4w*>(D + 4 * i) = v4w{0u, 0u, 0u, 0u};
+  if (i0 < (n & 3)) D[(n & ~int64_t(3)) + i0] = 0u;
+  for (int64_t i = i0; i < nrec; i += stride) rec[i] = 0ull;
+}
 
 // Before a block's ticket: wait until this thread's atomics on the sums are
 // performed.  The block that takes the last ticket reads the sums with
@@ -570,9 +659,25 @@ hipError_t launch_gram_bits(const u64* bits, int64_t W, int64_t ld, int32_t E, i
   return hipGetLastError();
 }
 
-hipError_t launch_finalize(const uint32_t* cacc, uint32_t* D, do_loss_result* out, int32_t E, int32_t L,
-                           hipStream_t s) {
-  hipLaunchKernelGGL(k_finalize, dim3((unsigned)L), dim3(1024), 0, s, cacc, D, out, E);
+hipError_t launch_clear(uint32_t* D, do_loss_result* out, int32_t E, int32_t L, hipStream_t s) {
+  const int64_t n = (int64_t)L * E * E, nrec = out != nullptr ? (int64_t)L * (sizeof(do_loss_result) / 8) : 0;
+  const int64_t work = std::max<int64_t>((n >> 2) + 1, nrec);
+  const int64_t blocks = std::min<int64_t>((work + 255) / 256, 4096);
+  hipLaunchKernelGGL(k_clear, dim3((unsigned)blocks), dim3(256), 0, s, D, n, reinterpret_cast<u64*>(out), nrec);
+  return hipGetLastError();
+}
+
+hipError_t launch_finalize(uint32_t* D, do_loss_result* out, int32_t E, int32_t L, hipStream_t s) {
+  if (E <= kOneBlockE) {
+    hipLaunchKernelGGL(k_finalize, dim3((unsigned)L), dim3(1024), 0, s, D, D, out, E);
+    return hipGetLastError();
+  }
+  const dim3 grid((unsigned)((E + kSplitRows - 1) / kSplitRows), (unsigned)L);
+  const size_t lds = (size_t)E * (kSplitRows + 1) * sizeof(uint32_t);
+  hipLaunchKernelGGL(k_finalize_rows, grid, dim3(kSplitRows * kWave), lds, s, D, out, E);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_finalize_close, dim3((unsigned)L), dim3(256), 0, s, D, out, E);
   return hipGetLastError();
 }
 

@@ -1388,6 +1388,10 @@ hipError_t launch_mode(int gm, const SegTable& tab, const PathArgs& a, bool fast
 
 }  // namespace
 
+// More than 256 experts and k <= kWideMaxK, signatures only (topk_wide.hip).
+constexpr int kWideMaxK = 16;
+hipError_t launch_wide(do_dtype dt, const SegTable& tab, const PathArgs& a, hipStream_t s, const ProfEv& pe);
+
 // The launches of the kRagged rows (topk_ragged.hip); gm: the Gram kind when a.cacc is given.
 hipError_t launch_ragged(do_dtype dt, int gm, const SegTable& tab, const PathArgs& a, bool fast, Sched sc,
                          hipStream_t s, const ProfEv& pe);
