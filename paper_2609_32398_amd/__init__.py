@@ -20,6 +20,7 @@ Functions keep the C names:
 """
 from __future__ import annotations
 
+import array
 import ctypes
 import os
 
@@ -158,6 +159,14 @@ def _scores_3d(scores: torch.Tensor, name: str = "scores"):
     if scores.dim() == 2:
         return 1, scores.shape[0], scores.shape[1]
     return scores.shape[0], scores.shape[1], scores.shape[2]
+
+
+def _int32_array(values, n: int):
+    """`values` as a host int32 array for the length of the call."""
+    try:  # 3 us for 256 Python ints; int() on each takes 20 us
+        return (ctypes.c_int32 * n).from_buffer(array.array("i", values))
+    except (TypeError, OverflowError):  # values that only int() converts
+        return (ctypes.c_int32 * n)(*[int(v) for v in values])
 
 
 def _units(N: int) -> int:
@@ -311,7 +320,7 @@ def do_load_stats(bits: torch.Tensor, N: int, k: int, p: torch.Tensor | None = N
     if expert_rank is not None:
         if len(expert_rank) != E:
             raise ValueError(f"expert_rank has {len(expert_rank)} entries, expected E = {E}")
-        rk = (ctypes.c_int32 * E)(*[int(r) for r in expert_rank])
+        rk = _int32_array(expert_rank, E)
     if p is not None:
         _want(p, "p", shape=(L, N, E) if p.dim() == 3 else (N, E), dtypes=_SCORE_DTYPES)
         if p.dim() == 2 and L != 1:
@@ -378,7 +387,7 @@ REM_MOVE_WORDS = 3  # do_rem_move: 24 bytes = 3 int64 words
 def _rank_array(expert_rank, E: int):
     if expert_rank is None or len(expert_rank) != E:
         raise ValueError(f"expert_rank must list the home rank of each of the E = {E} experts")
-    return (ctypes.c_int32 * E)(*[int(r) for r in expert_rank])
+    return _int32_array(expert_rank, E)
 
 
 def do_rem_allocate(expert_tokens: torch.Tensor, expert_rank, R: int, D: int, rank_load: torch.Tensor | None = None,
