@@ -22,9 +22,9 @@
 // "Positive" keys use the raw bit pattern (one instruction, exact whenever the
 // k-th score is a positive number); "general" keys first map the pattern to
 // an order-preserving integer (exact for all non-NaN values except that -0
-// sorts one step below +0).  An fp32 wave starts with positive keys and
-// switches to general keys for the rest of its tiles after meeting a
-// non-positive threshold; bf16 waves use general keys throughout.  bf16 keys keep all 16 value bits; fp32 keys keep 24, so a token
+// sorts one step below +0).  A wave starts with positive keys and switches to
+// general keys for the rest of its tiles after meeting a non-positive
+// threshold.  bf16 keys keep all 16 value bits; fp32 keys keep 24, so a token
 // whose k-th and (k+1)-th keys share a 24-bit bucket is settled by the whole
 // wave from the full values of that bucket.  A token whose threshold lands on
 // +-0, +-inf or NaN, or is not positive under positive keys, is re-ranked by
@@ -198,10 +198,108 @@ __device__ __forceinline__ void key_bf16x2(uint32_t x, uint32_t idx, int h, cons
   hi = (int)perm(x, idx, ks.hi[h]);
 }
 
+// bf16 ranking by pairs.  One insertion costs eight instructions per key, and
+// a pair of neighbouring experts can only place its smaller key in the list
+// when its larger one is there.  So each chunk ranks the larger keys of its
+// pairs (half the insertions) in a list of its own, then reads the eight pairs
+// in that list back from LDS and inserts their smaller keys, and merges the
+// list into the row's: about 6.5 instructions per key instead of 9 (positive
+// keys) or 10 (all VALU instructions of the kernel at 128 experts: -26 %; 48
+// layers x 262,144 tokens: 740 -> 683 us, with the loads spread over the
+// ranking and the drains of or_bit and unit_barrier gone).  A pair's key carries the index byte of its first expert; pairs
+// are disjoint index ranges, so equal values still rank by the lower index.
+//
+// The keys of the four pairs of a 16-byte piece.
+template <bool GEN>
+__device__ __forceinline__ uint32_t order_bf16x2(uint32_t x) {
+  if (GEN) {
+    const v2s s = __builtin_bit_cast(v2s, x) >> (short)15;
+    x ^= __builtin_bit_cast(uint32_t, s) & 0x7FFF7FFFu;
+  }
+  return x;
+}
+
+template <bool GEN>
+__device__ __forceinline__ void pair_keys(v4u x, uint32_t idx0, uint32_t idx1, const KeySel& ks, int (&g)[4]) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const uint32_t u = order_bf16x2<GEN>(x[i]);
+    uint32_t m;  // both halves: the larger of the two
+    asm("v_pk_max_i16 %0, %1, %1 op_sel:[0,1] op_sel_hi:[1,0]" : "=v"(m) : "v"(u));
+    g[i] = (int)perm(m, i < 2 ? idx0 : idx1, ks.lo[i & 1]);
+  }
+}
+
+// Insert x into the descending list of min(n, 8) entries (n a constant).
+__device__ __forceinline__ void insert_pair(int (&l)[8], int x, int n) {
+  if (n >= 8) {
+    int none = 0;
+    insert8<false>(l, x, none);
+    return;
+  }
+  if (n > 0) l[n] = min(l[n - 1], x);
+#pragma unroll
+  for (int i = 6; i > 0; --i)
+    if (i < n) l[i] = med3(l[i], l[i - 1], x);
+  l[0] = n > 0 ? max(l[0], x) : x;
+}
+
+// The eight pair keys of a chunk become the chunk's eight largest keys.  The
+// dword of position p of the chunk lies at row + (2p ^ sw); chunk_bytes is a
+// power of two; the index byte of a key is 255 - p modulo chunk_bytes / 2.
+// The smaller key of entry i ranks below the entries 0..i, so its insertion
+// starts at i + 1.
+template <bool GEN>
+__device__ __forceinline__ void resolve_pairs(int (&l)[8], const unsigned char* row, uint32_t sw, uint32_t chunk_bytes) {
+  const uint32_t mask = chunk_bytes - 2, inv = sw ^ mask;
+  uint32_t x[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) x[i] = *reinterpret_cast<const uint32_t*>(row + ((((uint32_t)l[i] << 1) & mask) ^ inv));
+  int lose[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const uint32_t u = order_bf16x2<GEN>(x[i]);
+    const int a = (int)__builtin_amdgcn_perm(u, (uint32_t)l[i], 0x05040C00u);
+    const int b = (int)__builtin_amdgcn_perm(u, (uint32_t)l[i] - 1u, 0x07060C00u);
+    l[i] = max(a, b);
+    lose[i] = min(a, b);
+  }
+#pragma unroll
+  for (int i = 0; i < 7; ++i)
+#pragma unroll
+    for (int j = 7; j > i; --j) l[j] = med3(l[j], l[j - 1], lose[i]);
+}
+
+// The eight largest of two descending lists into top (first: top is empty): the
+// element-wise maxima with one list reversed are those eight as a bitonic
+// sequence, sorted by three rounds.
+__device__ __forceinline__ void merge8(int (&top)[8], const int (&l)[8], bool first) {
+  if (first) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) top[i] = l[i];
+    return;
+  }
+  int m[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) m[i] = max(top[i], l[7 - i]);
+#pragma unroll
+  for (int d = 4; d > 0; d >>= 1)
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      if ((i & d) == 0) {
+        const int hi = max(m[i], m[i + d]), lo = min(m[i], m[i + d]);
+        m[i] = hi;
+        m[i + d] = lo;
+      }
+#pragma unroll
+  for (int i = 0; i < 8; ++i) top[i] = m[i];
+}
+
 // Rank one staged 128-byte chunk (vectors cv0..cv0+7 of the lane's row) into top/rej.
-template <typename T, bool GEN>
+// issue(v) is called once after each piece v: a part of the next chunk's loads.
+template <typename T, bool GEN, typename F>
 __device__ __forceinline__ void rank_chunk(const unsigned char* sbuf, int lane, int cv0, const KeySel& ks,
-                                           int (&top)[8], int& rej) {
+                                           int (&top)[8], int& rej, F&& issue) {
   const unsigned char* row = sbuf + lane * 128;
   const int sw = row_swizzle(lane);
   auto piece = [&](int q) { return *reinterpret_cast<const v4u*>(row + ((q ^ sw) << 4)); };
@@ -225,6 +323,7 @@ __device__ __forceinline__ void rank_chunk(const unsigned char* sbuf, int lane, 
       g[3] = key_f32<GEN>(x.w, idx[q], ks.f32[3]);
 #pragma unroll
       for (int i = 0; i < 4; ++i) insert8<!Traits<T>::kExact>(top, g[i], rej);
+      issue(q);
       x = xn;
     }
   } else {
@@ -234,17 +333,17 @@ __device__ __forceinline__ void rank_chunk(const unsigned char* sbuf, int lane, 
 #pragma unroll
     for (int v = 0; v < 8; ++v) xs[v] = piece(v);
     __builtin_amdgcn_sched_barrier(0);  // keep the reads ahead of the ranking
+    int fr[8];
 #pragma unroll
     for (int v = 0; v < 8; ++v) {
-      int g[8];
-      const v4u x = xs[v];
-      key_bf16x2<GEN>(x.x, idx[2 * v], 0, ks, g[0], g[1]);
-      key_bf16x2<GEN>(x.y, idx[2 * v], 1, ks, g[2], g[3]);
-      key_bf16x2<GEN>(x.z, idx[2 * v + 1], 0, ks, g[4], g[5]);
-      key_bf16x2<GEN>(x.w, idx[2 * v + 1], 1, ks, g[6], g[7]);
+      int g[4];
+      pair_keys<GEN>(xs[v], idx[2 * v], idx[2 * v + 1], ks, g);
 #pragma unroll
-      for (int i = 0; i < 8; ++i) insert8<false>(top, g[i], rej);
+      for (int i = 0; i < 4; ++i) insert_pair(fr, g[i], 4 * v + i);
+      issue(v);
     }
+    resolve_pairs<GEN>(fr, row, (uint32_t)(sw << 4), 128);
+    merge8(top, fr, cv0 == 0);
   }
 }
 
@@ -280,16 +379,53 @@ __device__ __forceinline__ int stage_swz(int r, int lg) { return (r >> (4 - lg))
 // Rank the first nv pieces of a staged chunk; the piece `tail_q` (-1: none) is
 // the row's last 16 bytes, of which the first `dup` bytes repeat elements of
 // the piece before it: they are set to all ones (a NaN, ranked last and never
-// selected on the fast path), and its experts are E - kVec ... E - 1.
+// selected on the fast path), and its experts are E - kVec ... E - 1.  The
+// index byte of an fp32 key is 255 - expert, that of a bf16 key 255 - position
+// in the staged pieces (the selection takes dup / 2 off the tail's positions).
+// bf16 chunks of at least kPairPieces pieces are ranked by pairs: at three
+// pieces the second half's 24 insertions just pay for reading the pairs back.
+constexpr int kPairPieces = 4;
 template <typename T, bool GEN, int kPieces>
-__device__ __forceinline__ void rank_staged(const unsigned char* sbuf, int lane, int lg, int cv0, int nv, int tail_q,
+__device__ __forceinline__ void rank_staged(unsigned char* sbuf, int lane, int lg, int cv0, int nv, int tail_q,
                                             int dup, int E, const KeySel& ks, int (&top)[8], int& rej) {
-  const unsigned char* row = sbuf + (lane << (4 + lg));
+  unsigned char* row = sbuf + (lane << (4 + lg));
   const int sw = stage_swz(lane, lg) << 4;
   constexpr int kV = Traits<T>::kVec;
   // the next piece is read while the current one is ranked (unconditionally: a
   // piece past nv re-reads the last one)
   auto piece = [&](int q) { return *reinterpret_cast<const v4u*>(row + ((min(q, nv - 1) << 4) ^ sw)); };
+  auto void_dup = [&](v4u& x) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int b = dup - 4 * i;  // bytes of dword i to void: 0, 2 or 4
+      x[i] |= b >= 4 ? ~0u : b == 2 ? 0xFFFFu : 0u;
+    }
+  };
+  if (Traits<T>::kExact && kPieces == 8 && nv >= kPairPieces) {
+    if (tail_q >= 0) {  // in the stage buffer too: resolve_pairs reads it again
+      v4u x = piece(tail_q);
+      void_dup(x);
+      *reinterpret_cast<v4u*>(row + ((tail_q << 4) ^ sw)) = x;
+    }
+    int fr[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) fr[i] = INT_MIN;
+    v4u xn = piece(0);
+#pragma unroll
+    for (int q = 0; q < kPieces; ++q) {
+      if (q >= nv) break;  // wave-uniform
+      const v4u x = xn;
+      xn = piece(q + 1);
+      const int e0 = (cv0 + q) * kV;
+      int g[4];
+      pair_keys<GEN>(x, idx_bytes(e0), idx_bytes(e0 + 4), ks, g);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) insert_pair(fr, g[i], 4 * q + i);
+    }
+    resolve_pairs<GEN>(fr, row, (uint32_t)sw, 16 * kPieces);
+    merge8(top, fr, cv0 == 0);
+    return;
+  }
   v4u xn = piece(0);
 #pragma unroll
   for (int q = 0; q < kPieces; ++q) {
@@ -298,12 +434,8 @@ __device__ __forceinline__ void rank_staged(const unsigned char* sbuf, int lane,
     xn = piece(q + 1);
     int e0 = (cv0 + q) * kV;
     if (q == tail_q) {
-      e0 = E - kV;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int b = dup - 4 * i;  // bytes of dword i to void: 0, 2 or 4
-        x[i] |= b >= 4 ? ~0u : b == 2 ? 0xFFFFu : 0u;
-      }
+      if (!Traits<T>::kExact) e0 = E - kV;
+      void_dup(x);
     }
     rank_piece<T, GEN>(x, idx_bytes(e0), kV == 8 ? idx_bytes(e0 + 4) : 0u, ks, top, rej);
   }
@@ -731,6 +863,21 @@ __device__ __attribute__((noinline)) void mfma_flush_ool(typename Mfma<TS>::Acc 
 
 #define DOL_WAVE_FENCE() asm volatile("" ::: "memory")
 
+// OR `bit` into a signature word of the bit tile.  The compiler waits for every
+// direct-to-LDS load in flight before an LDS atomic or a __syncthreads, that is
+// for the next unit's first chunk.  The tile is no target of those loads, so
+// the Top-K kernel uses this form, and unit_barrier instead of __syncthreads.
+__device__ __forceinline__ void or_bit(u64* word, u64 bit) {
+  const uint32_t addr = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) u64*)word;
+  asm volatile("ds_or_b64 %0, %1" ::"v"(addr), "v"(bit) : "memory");
+}
+
+// The block's barrier for LDS alone: this wave's LDS operations are complete
+// before it, its loads and stores of global memory may still be in flight.
+__device__ __forceinline__ void unit_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
 // One segment as the kernel sees it (all values wave-uniform).  Counts fit
 // 32 bits: a segment holds fewer than 2^32 tokens and its bit positions stay
 // below 2^32, so word indices are below 2^26 and unit indices below 2^29.
@@ -916,6 +1063,18 @@ __global__ __launch_bounds__(kFusedThreads) void k_topk(const SegTable tab_arg, 
     const int64_t rem = (int64_t)sg.sh + (int64_t)sg.n - ((int64_t)wl << 6);
     r_hi = (int)max((int64_t)0, min((int64_t)64, rem));
   };
+  // Load j of the chunk at cbase: rows 8j .. 8j + 7.
+  auto dma_row8 = [&](const unsigned char* cbase, int j, unsigned char* sbuf) __attribute__((always_inline)) {
+    const __amdgpu_buffer_rsrc_t rs =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(cbase), (short)0, 0x7FFFFFFF, kBufWord3);
+    if constexpr (kVoff)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)(sbuf + j * 1024), 16,
+                                               voff[j], 0, 0, kStreamPolicy);
+    else
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)(sbuf + j * 1024), 16,
+                                               (j & 1) ? off_odd : off_even, (uint32_t)(j * 8 * rowB), 0,
+                                               kStreamPolicy);
+  };
   // Direct-to-LDS load of full 128-byte chunk c_ of the 64 rows of local word
   // wl of segment sg (asynchronous; the consumer waits with DOL_WAIT_VMEM).
   // When every row lies inside the segment the loads go through a buffer
@@ -925,17 +1084,8 @@ __global__ __launch_bounds__(kFusedThreads) void k_topk(const SegTable tab_arg, 
   auto dma = [&](const Seg& sg, uint32_t wl, int c_, unsigned char* sbuf) {
     const unsigned char* cbase = word_rows(sg, wl, rowB) + c_ * 128;  // row 0 of the chunk (uniform)
     if (AL || (wl >= sg.full_lo && wl < sg.full_hi)) {  // every row inside the segment
-      const __amdgpu_buffer_rsrc_t rs =
-          __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(cbase), (short)0, 0x7FFFFFFF, kBufWord3);
 #pragma unroll
-      for (int j = 0; j < 8; ++j)
-        if constexpr (kVoff)
-          __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)(sbuf + j * 1024), 16,
-                                                   voff[j], 0, 0, kStreamPolicy);
-        else
-          __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)(sbuf + j * 1024), 16,
-                                                   (j & 1) ? off_odd : off_even, (uint32_t)(j * 8 * rowB), 0,
-                                                   kStreamPolicy);
+      for (int j = 0; j < 8; ++j) dma_row8(cbase, j, sbuf);
     } else {
       int r_lo, r_hi;
       row_bounds(sg, wl, r_lo, r_hi);
@@ -1137,13 +1287,12 @@ __global__ __launch_bounds__(kFusedThreads) void k_topk(const SegTable tab_arg, 
     }
   };
 
-  // fp32 waves start with positive keys (general keys cost ~3 more
-  // instructions per score) and switch for the rest of the kernel after
-  // meeting a non-positive threshold; bf16 general keys cost ~1 more per
-  // score, less than the exact re-rank a first non-positive threshold costs
-  // in a short launch, so bf16 rows start with them and move to positive
-  // keys within the row (below).
-  bool gen = Traits<T>::kExact;
+  // Waves start with positive keys (general keys cost ~3 more instructions per
+  // fp32 score, ~1 per bf16 score) and switch for the rest of the kernel after
+  // meeting a non-positive threshold: fp32 at the end of the row, which is then
+  // re-ranked exactly; bf16 after the row's first chunk, which is ranked again
+  // from LDS.
+  bool gen = false;
   int cb = 0;  // stage buffer holding the current chunk
   // key byte selectors, opaque to the compiler so that they stay in VGPRs
   // instead of being rematerialised for every key
@@ -1229,28 +1378,51 @@ __global__ __launch_bounds__(kFusedThreads) void k_topk(const SegTable tab_arg, 
             DOL_WAIT_VMEM();  // this chunk's direct-to-LDS loads (and earlier stores) have completed
           DOL_WAVE_FENCE();
           unsigned char* other = st + (cb ^ 1) * kChunkBytes;
-          if (c + 1 < nch)
-            load_chunk(sv, wl, c + 1, other);
-          else if (next_mine)
-            load_chunk(svn, wln, 0, other);
+          // kAligned: the eight loads of the next chunk are issued one after each
+          // ranked piece.  Issued together they queued behind those of the other
+          // waves and held up waves 4-7 for 18 % of their time.  After the block's
+          // last chunk they read the current chunk once more, into a free buffer.
+          const unsigned char* nrow = word_rows(sv, wl, rowB) + (c + 1 < nch ? c + 1 : c) * 128;
+          if (c + 1 == nch && next_mine) nrow = word_rows(svn, wln, rowB);
+          auto issue = [&](int v) __attribute__((always_inline)) {
+            if constexpr (AL) {
+              __builtin_amdgcn_sched_barrier(0);
+              dma_row8(nrow, v, other);
+              __builtin_amdgcn_sched_barrier(0);
+            }
+          };
+          if constexpr (!AL) {
+            if (c + 1 < nch)
+              load_chunk(sv, wl, c + 1, other);
+            else if (next_mine)
+              load_chunk(svn, wln, 0, other);
+          }
           if (!stored) {
             store_share(pbt);
             stored = true;
           }
           if constexpr (Traits<T>::kExact)
             if (wave >= 4 && !(c & 1)) __builtin_amdgcn_s_setprio(1);
-          if constexpr (RG) {
-            const int nv = (min(CB, rowB - CB * c) + 15) >> 4;
-            const int tail_q = dup != 0 && c + 1 == nch ? nv - 1 : -1;
-            if (gk)
-              rank_staged<T, true, kPieces>(cur, lane, lg, c * kPieces, nv, tail_q, dup, E, ks, top, rej);
-            else
-              rank_staged<T, false, kPieces>(cur, lane, lg, c * kPieces, nv, tail_q, dup, E, ks, top, rej);
-          } else {
-            if (gk)
-              rank_chunk<T, true>(cur, lane, c * 8, ks, top, rej);
-            else
-              rank_chunk<T, false>(cur, lane, c * 8, ks, top, rej);
+          for (;;) {
+            if constexpr (RG) {
+              const int nv = (min(CB, rowB - CB * c) + 15) >> 4;
+              const int tail_q = dup != 0 && c + 1 == nch ? nv - 1 : -1;
+              if (gk)
+                rank_staged<T, true, kPieces>(cur, lane, lg, c * kPieces, nv, tail_q, dup, E, ks, top, rej);
+              else
+                rank_staged<T, false, kPieces>(cur, lane, lg, c * kPieces, nv, tail_q, dup, E, ks, top, rej);
+            } else {
+              if (gk)
+                rank_chunk<T, true>(cur, lane, c * 8, ks, top, rej, issue);
+              else
+                rank_chunk<T, false>(cur, lane, c * 8, ks, top, rej, issue);
+            }
+            if (!Traits<T>::kExact || gk || c > 0 ||
+                __ballot(valid && top[7] < Traits<T>::kPosMin) == 0ull)
+              break;
+            gen = gk = true;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) top[i] = INT_MIN;
           }
           // bf16: once the 8th key of every token of the wave is a positive
           // number, the rest of the row takes positive keys.  A negative score
@@ -1284,7 +1456,7 @@ __global__ __launch_bounds__(kFusedThreads) void k_topk(const SegTable tab_arg, 
         }
         bool ok = top[0] < kCompPosInf;
         bool nonpos = false;
-        if (gen) {
+        if (Traits<T>::kExact || gen) {  // (bf16: a list of positive keys passes both)
           ok = ok && sk > kCompNegInfMax && (sk < Traits<T>::kZeroLo || sk > Traits<T>::kZeroHi);
         } else {
           nonpos = valid && sk < Traits<T>::kPosMin;
@@ -1304,12 +1476,15 @@ __global__ __launch_bounds__(kFusedThreads) void k_topk(const SegTable tab_arg, 
         int need = 0;
         const bool sel = valid && ok;
         const u64 bit = sel ? 1ull << lane : 0ull;
+        const int tail_pos = RG && Traits<T>::kExact && dup != 0 ? (rowB + dup - 16) / (int)sizeof(T) : kFastMaxE;
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
           if (i >= k) break;  // wave-uniform
           const bool tied = !Traits<T>::kExact && tie && (top[i] >> 8) == (sk >> 8);
           need += tied ? 1 : 0;
-          atomicOr(&mybt[((255 - (top[i] & 255)) & (EPW - 1)) ^ bt_swz(wave)], tied ? 0ull : bit);
+          int e = 255 - (top[i] & 255);
+          if constexpr (RG && Traits<T>::kExact) e -= e >= tail_pos ? dup / (int)sizeof(T) : 0;
+          or_bit(&mybt[(e & (EPW - 1)) ^ bt_swz(wave)], tied ? 0ull : bit);
         }
         if (!Traits<T>::kExact) {
           const u64 tm = __ballot(tie);
@@ -1325,7 +1500,7 @@ __global__ __launch_bounds__(kFusedThreads) void k_topk(const SegTable tab_arg, 
     // waves without a fast chunk loop in this unit finish the pending unit here
     if (!stored) store_share(pbt);
     if (gram_done < kFusedWaves) gram_slots(pbt, gram_done, kFusedWaves);
-    __syncthreads();  // this unit's bit tile is complete; the pending unit's tile is free
+    unit_barrier();  // this unit's bit tile is complete; the pending unit's tile is free
     // the fp32 Gram accumulators hold exact counts below 2^24: flush at a
     // layer change and before a block has accumulated 2^24 tokens
     if (have_pend && (pend.layer != sv.layer || ++acc_units >= kMaxAccUnits)) {
@@ -1344,6 +1519,9 @@ __global__ __launch_bounds__(kFusedThreads) void k_topk(const SegTable tab_arg, 
     sv = svn;
     tl0 = tl0n;
   }
+  // no load may still write this block's LDS when it ends (issue re-reads a
+  // chunk after the last one)
+  DOL_WAIT_VMEM();
   // the last unit
   store_share(bt_all + (buf ^ 1) * kFusedWaves * EPW);
   batch_flush();
