@@ -60,7 +60,7 @@ hipError_t launch_ep(RowMode mode, const SegTable& tab, const PathArgs& a, Sched
 // launches below kTuneMinUnits use the first candidate (or the one already
 // chosen for the shape); a capture never touches the measurement events.
 // When every slot of the table holds a shape, a decided one is recycled.
-constexpr Sched kSchedCand[2] = {Sched{4, true}, Sched{0, false}};  // XCD partitions; contiguous ranges
+constexpr Sched kSchedCand[2] = {Sched{4, 3}, Sched{0, 0}};  // XCD partitions; contiguous ranges
 constexpr int kNumCand = 2;
 constexpr int64_t kTuneMinUnits = 1024;  // 512 Ki tokens
 constexpr int kTuneTrials = 3;           // measured launches per candidate
@@ -397,7 +397,10 @@ hipError_t launch_topk(do_dtype dt, SegTable& tab, int nseg, const PathArgs& a, 
   const RowMode mode = !vec_rows || rowB % 128 != 0 || !fast ? kRagged : aligned_segments(tab) ? kAligned : kDirect;
   hipEvent_t ev[2] = {nullptr, nullptr};
   const int forced = g_opt_sched.load(std::memory_order_relaxed);
-  const Sched sc = forced >= 0 ? kSchedCand[forced] : tuned_schedule(dt, tab, a, mode, fast, s, ev);
+  Sched sc = forced >= 0 ? kSchedCand[forced] : tuned_schedule(dt, tab, a, mode, fast, s, ev);
+  // partitions of at least one layer each: fewer Gram flushes per block (k_topk)
+  const int layers = tab.s[nseg - 1].layer - tab.s[0].layer + 1;
+  if (sc.lp == 3 && a.cacc != nullptr) sc.lp = layers >= 32 ? 5 : layers >= 16 ? 4 : 3;
   // a tuner trial binds its events to the dispatch (the kernel alone), unless
   // the caller's timing events already are; then they go around the launch
   ProfEv use = pe;

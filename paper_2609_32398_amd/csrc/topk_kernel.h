@@ -51,10 +51,10 @@
 namespace dol {
 
 // Unit schedule of the Top-K kernel: groups of gu consecutive units (gu = 0:
-// one contiguous range per block), in one partition or one per XCD.
+// one contiguous range per block), in 2^lp partitions (lp = 3: one per XCD).
 struct Sched {
   int64_t gu;
-  bool xcd;
+  int lp;
 };
 
 namespace {
@@ -344,6 +344,20 @@ __device__ __forceinline__ void rank_chunk(const unsigned char* sbuf, int lane, 
     }
     resolve_pairs<GEN>(fr, row, (uint32_t)(sw << 4), 128);
     merge8(top, fr, cv0 == 0);
+  }
+}
+
+// The k-th key of a list (k uniform, at most 8).
+__device__ __forceinline__ int kth_key(const int (&top)[8], int k) {
+  switch (k) {
+    case 1: return top[0];
+    case 2: return top[1];
+    case 3: return top[2];
+    case 4: return top[3];
+    case 5: return top[4];
+    case 6: return top[5];
+    case 7: return top[6];
+    default: return top[7];
   }
 }
 
@@ -940,7 +954,7 @@ __device__ __forceinline__ const unsigned char* word_rows(const Seg& sg, uint32_
 // after each ranked chunk), so they overlap other waves' ranking instead of
 // following every barrier at once.  Gram accumulators are flushed when the
 // layer changes and at the end.  flags bit 0: fast path allowed (16-byte
-// rows, k <= 8, E <= 256); bit 1: XCD-partitioned schedule.  gu: units per
+// rows, k <= 8, E <= 256); above: log2 of the schedule's partitions.  gu: units per
 // schedule group.
 // ---------------------------------------------------------------------------
 // How a launch's score rows reach LDS (chosen by launch_gm).
@@ -995,22 +1009,28 @@ __global__ __launch_bounds__(kFusedThreads) void k_topk(const SegTable tab_arg, 
   // Unit schedule: the unit range [lo, hi) of a block's partition is cut into
   // groups of `gu` consecutive units, and the Gs blocks of the partition take
   // groups pos, pos + Gs, pos + 2 Gs, ...  Contiguous ranges are the case of
-  // one group per block.  flags bit 1 selects the partition:
+  // one group per block.  the flags above bit 0 select the partitions
+  // (2^lp of them, lp when the grid divides evenly, else 0):
   //   0: one partition [0, U), pos = b
-  //   1: eight partitions, one per XCD (blocks are dispatched round-robin,
+  //   3: eight partitions, one per XCD (blocks are dispatched round-robin,
   //      so block b runs on XCD b mod 8), of U/8 units each; the XCD's
   //      blocks work on adjacent groups of its partition, so their signature
   //      stores land side by side while each block stays in few layers (few
   //      Gram flushes, and those of different XCDs go to different layers)
+  //   4, 5: two or four partitions per XCD, for 16 or 32 layers and more: each
+  //      block works in fewer layers still.  48 layers x 262,144 tokens, 128
+  //      experts: 690 us with 8 partitions (six flushes per block, 8 % of the
+  //      time), 649 us with 16, 636 us with 32.
   // All unit counts are below 2^29 (64 segments of fewer than 2^32 tokens).
   const uint32_t U = (uint32_t)tab->tile_start[tab->nseg];
   const uint32_t G = gridDim.x;
   const uint32_t b = blockIdx.x;
-  const bool xcd = (G & 7) == 0 && (flags & 2) != 0;
-  const uint32_t lo = xcd ? (uint32_t)(((uint64_t)(b & 7) * U) >> 3) : 0u;
-  const uint32_t hi = xcd ? (uint32_t)(((uint64_t)((b & 7) + 1) * U) >> 3) : U;
-  const uint32_t Gs = xcd ? G >> 3 : G;
-  const uint32_t pos = xcd ? b >> 3 : b;
+  const int lp = (G & ((1u << (flags >> 1)) - 1)) == 0 ? flags >> 1 : 0;
+  const uint32_t part = b & ((1u << lp) - 1);
+  const uint32_t lo = (uint32_t)(((uint64_t)part * U) >> lp);
+  const uint32_t hi = (uint32_t)(((uint64_t)(part + 1) * U) >> lp);
+  const uint32_t Gs = G >> lp;
+  const uint32_t pos = b >> lp;
   const uint32_t ug = lo + pos * gu;
   if (ug >= hi) return;
   // The unit after u in this block's schedule (U when there is none), from
@@ -1289,9 +1309,10 @@ __global__ __launch_bounds__(kFusedThreads) void k_topk(const SegTable tab_arg, 
 
   // Waves start with positive keys (general keys cost ~3 more instructions per
   // fp32 score, ~1 per bf16 score) and switch for the rest of the kernel after
-  // meeting a non-positive threshold: fp32 at the end of the row, which is then
-  // re-ranked exactly; bf16 after the row's first chunk, which is ranked again
-  // from LDS.
+  // meeting a non-positive threshold.  bf16 rows and fp32 rows of one chunk look
+  // at it after the first chunk and rank that again from LDS (8 fp32 experts,
+  // 4,096 tokens, where nearly every wave meets one: 21.5 -> 16.4 us); longer fp32 rows
+  // look at their end, and those tokens are re-ranked exactly.
   bool gen = false;
   int cb = 0;  // stage buffer holding the current chunk
   // key byte selectors, opaque to the compiler so that they stay in VGPRs
@@ -1417,10 +1438,11 @@ __global__ __launch_bounds__(kFusedThreads) void k_topk(const SegTable tab_arg, 
               else
                 rank_chunk<T, false>(cur, lane, c * 8, ks, top, rej, issue);
             }
-            if (!Traits<T>::kExact || gk || c > 0 ||
-                __ballot(valid && top[7] < Traits<T>::kPosMin) == 0ull)
+            if (gk || c > 0 || !(Traits<T>::kExact || nch == 1) ||
+                __ballot(valid && kth_key(top, k) < Traits<T>::kPosMin) == 0ull)
               break;
             gen = gk = true;
+            rej = INT_MIN;
 #pragma unroll
             for (int i = 0; i < 8; ++i) top[i] = INT_MIN;
           }
@@ -1443,8 +1465,12 @@ __global__ __launch_bounds__(kFusedThreads) void k_topk(const SegTable tab_arg, 
         if (wave >= 4) __builtin_amdgcn_s_setprio(0);
         // the k-th and (k+1)-th keys: a wave-uniform branch on k, so that no
         // per-position predicate on k stays live (in registers) across the loop
+        // (opaque: a comparison per position hoisted out of the unit loop takes
+        // two SGPRs each, which spilled)
+        int ks_ = k;
+        asm volatile("" : "+s"(ks_));
         int sk, sk1;
-        switch (k) {
+        switch (ks_) {
           case 1: sk = top[0]; sk1 = top[1]; break;
           case 2: sk = top[1]; sk1 = top[2]; break;
           case 3: sk = top[2]; sk1 = top[3]; break;
@@ -1479,7 +1505,7 @@ __global__ __launch_bounds__(kFusedThreads) void k_topk(const SegTable tab_arg, 
         const int tail_pos = RG && Traits<T>::kExact && dup != 0 ? (rowB + dup - 16) / (int)sizeof(T) : kFastMaxE;
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-          if (i >= k) break;  // wave-uniform
+          if (i >= ks_) break;  // wave-uniform
           const bool tied = !Traits<T>::kExact && tie && (top[i] >> 8) == (sk >> 8);
           need += tied ? 1 : 0;
           int e = 255 - (top[i] & 255);
@@ -1544,10 +1570,11 @@ hipError_t launch_one(const SegTable& tab, const PathArgs& a, bool fast, Sched s
   int64_t blocks = std::min<int64_t>((int64_t)di.cu_count * occ, units);
   blocks = std::max<int64_t>(blocks, 1);
   int64_t gu = sc.gu;
-  const int64_t per_part = sc.xcd ? (units + 7) / 8 : units;
-  const int64_t gs = sc.xcd ? std::max<int64_t>(blocks / 8, 1) : blocks;
+  const int64_t parts = int64_t(1) << sc.lp;
+  const int64_t per_part = (units + parts - 1) / parts;
+  const int64_t gs = std::max<int64_t>(blocks / parts, 1);
   if (gu <= 0 || gu * gs > per_part) gu = (per_part + gs - 1) / gs;  // contiguous ranges
-  const int flags = (fast ? 1 : 0) | (sc.xcd ? 2 : 0);
+  const int flags = (fast ? 1 : 0) | (sc.lp << 1);
   if (pe.start != nullptr || pe.stop != nullptr)  // caller's timing events bound to this dispatch
     hipExtLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kFusedThreads), lds, s, pe.start, pe.stop, 0u, tab, a,
                           flags, (uint32_t)gu);

@@ -59,3 +59,36 @@ def test_pair_ranking(dl, orc, E, kind):
         F = orc.topk_signature(x, k)
         np.testing.assert_array_equal(bits_np(bits, N)[0], orc.pack(F))
         np.testing.assert_array_equal(D_np(D)[0], orc.hamming(F))
+
+
+@pytest.mark.parametrize("E", [8, 24, 32])
+@pytest.mark.parametrize("k", [1, 2, 7, 8])
+def test_one_chunk_fp32_rows(dl, orc, E, k):
+    """fp32 rows of one chunk whose k-th score is negative, zero or special in some tokens."""
+    for kind in ("normal", "few", "special"):
+        x = (_scores(kind, 577, E).astype(np.uint32) << 16).view(np.float32)
+        print(f"[case] one chunk fp32 E={E} k={k} {kind}", flush=True)
+        bits, D, _ = dl.do_fused(to_dev(x), k, want_bits=True)
+        torch.cuda.synchronize()
+        F = orc.topk_signature(x, k)
+        np.testing.assert_array_equal(bits_np(bits, 577)[0], orc.pack(F))
+        np.testing.assert_array_equal(D_np(D)[0], orc.hamming(F))
+
+
+@pytest.mark.parametrize("L,N", [(16, 8192), (33, 4096), (33, 1000), (64, 513), (70, 2048)])
+def test_layer_partitions(dl, orc, L, N):
+    """8, 16 and 32 schedule partitions, grids that they divide or not, two launches (70 layers)."""
+    E, k = 64, 6
+    x = np.stack([_scores("normal", N, E) if l % 5 else _scores("pairs", N, E) for l in range(L)])
+    x[1::2] = np.roll(x[1::2], 3, axis=2)
+    print(f"[case] partitions L={L} N={N}", flush=True)
+    bits, D, _ = dl.do_fused(to_dev(x), k, want_bits=True)
+    torch.cuda.synchronize()
+    got, dist = bits_np(bits, N), D_np(D)
+    for l in {0, 1, L // 2, L - 1}:
+        F = orc.topk_signature(x[l], k)
+        np.testing.assert_array_equal(got[l], orc.pack(F))
+        np.testing.assert_array_equal(dist[l], orc.hamming(F))
+    for l in range(2, L):  # the other layers repeat the first ones
+        j = next(m for m in range(l + 1) if (m % 5 == 0) == (l % 5 == 0) and m % 2 == l % 2)
+        np.testing.assert_array_equal(dist[l], dist[j])
