@@ -202,8 +202,8 @@ Sched tuned_schedule(do_dtype dt, const SegTable& tab, const PathArgs& a, RowMod
 }
 
 // ---------------------------------------------------------------------------
-// Gram of stored signatures (do_pairwise_hamming, E <= 256) on the same fp4
-// MFMA tiles as k_topk.  Block b takes layer b / bpl and the part b % bpl of
+// Gram of stored signatures (do_pairwise_hamming; which sizes: launch_gram_mfma)
+// on the same fp4 MFMA tiles as k_topk.  Block b takes layer b / bpl and the part b % bpl of
 // that layer's 8-word chunks, kGramGroup chunks per step.  A chunk's words of
 // every expert are staged in LDS in the bit-tile layout of k_topk (word s of
 // expert e at s * EPW + (e ^ bt_swz(s))); the next step's words are loaded
@@ -272,6 +272,121 @@ __global__ __launch_bounds__(kFusedThreads) void k_gram_mfma(const u64* bits, in
     buf ^= 1;
   }
   mfma_flush<GS::TS>(acc, wt, cacc + (int64_t)l * E * E, E, lane, (int)(blockIdx.x % kGP), pair64);
+}
+
+// ---------------------------------------------------------------------------
+// Gram of stored signatures up to 128 experts (NT tiles of 32).  Bound by the
+// matrix cores.  Every wave multiplies whole units by itself: lane l loads 32
+// bytes of expert l % 32 of each tile (its half l / 32 of the unit's words)
+// straight into the operand layout, so nothing is staged in LDS, no barrier
+// runs between units, and a word is expanded once for all NT (NT + 1) / 2
+// tile pairs instead of once per wave that uses its tile (k_gram_mfma: four
+// times at 128 experts).  The token order along k follows the lane halves and
+// is the same in both operands.  Loads run two units ahead.
+// do_pairwise_hamming of 48 layers x 262,144 tokens, k_gram_mfma -> this: 32
+// experts 55 -> 25 us, 64: 69 -> 39, 96: 135 -> 59, 128: 139 -> 84 to 87; one
+// layer of 1,048,576 tokens, 128 experts: 41 -> 36 us.
+// The units of all layers are split evenly over the blocks; a block sums its
+// four waves' counts in LDS and adds them at the end of a layer and at the
+// latest after kGramMaxChunks units, so that every sum is exact in fp32.
+// ---------------------------------------------------------------------------
+constexpr int kGuWaves = 4;
+
+template <int NT>
+__global__ __launch_bounds__(kGuWaves * kWave, 1) void k_gram_units(const u64* bits, int64_t W, int E, int L,
+                                                                    uint32_t* cacc, bool pair64) {
+  constexpr int NP = NT * (NT + 1) / 2;
+  typedef v4u v4u_any8 __attribute__((aligned(8)));
+  __shared__ float sum[NP][16][kWave];
+  const int lane = threadIdx.x & 63, half = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t last_on = (NT - 1) * 32 + (lane & 31) < E ? ~0u : 0u;  // the last tile's experts past E
+  const int64_t U = (W + 7) >> 3, T = (int64_t)L * U;
+  const int64_t t1 = (int64_t)((unsigned __int128)T * (blockIdx.x + 1) / gridDim.x);
+  for (int64_t t = (int64_t)((unsigned __int128)T * blockIdx.x / gridDim.x); t < t1;) {
+    const int64_t l = t / U, u0 = t - l * U;
+    const int64_t n = min(min(t1 - t, U - u0), kGramMaxChunks);
+    const u64* lb = bits + l * E * sig_words(W) + u0 * E * 8;
+    v16f acc[NP];
+#pragma unroll
+    for (int p = 0; p < NP; ++p)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[p][r] = 0.0f;
+    // unit i of the segment (past its end: the last one again, not multiplied)
+    auto load = [&](int64_t i, v4u (&r)[NT][2]) __attribute__((always_inline)) {
+      const u64* ub = lb + min(i, n - 1) * E * 8 + half * 4;
+#pragma unroll
+      for (int a = 0; a < NT; ++a) {
+        const v4u_any8* p = reinterpret_cast<const v4u_any8*>(ub + min(a * 32 + (lane & 31), E - 1) * 8);
+        r[a][0] = __builtin_nontemporal_load(p);
+        r[a][1] = __builtin_nontemporal_load(p + 1);
+      }
+    };
+    auto mult = [&](int64_t i, v4u (&r)[NT][2]) __attribute__((always_inline)) {
+      if (i >= n) return;
+#pragma unroll
+      for (int d = 0; d < 8; ++d) r[NT - 1][d >> 2][d & 3] &= last_on;
+      if (8 * (u0 + i) + 8 > W) {  // words past W
+#pragma unroll
+        for (int d = 0; d < 8; ++d) {
+          const uint32_t in = 8 * (u0 + i) + half * 4 + (d >> 1) < W ? ~0u : 0u;
+#pragma unroll
+          for (int a = 0; a < NT; ++a) r[a][d >> 2][d & 3] &= in;
+        }
+      }
+#pragma unroll
+      for (int d = 0; d < 8; ++d) {
+        v8i f[NT];
+#pragma unroll
+        for (int a = 0; a < NT; ++a) f[a] = expand32_fp4(r[a][d >> 2][d & 3]);
+        int p = 0;
+#pragma unroll
+        for (int a = 0; a < NT; ++a)
+#pragma unroll
+          for (int b = a; b < NT; ++b, ++p) acc[p] = Mfma<32>::mac(f[a], f[b], acc[p]);
+      }
+    };
+    v4u ra[NT][2], rb[NT][2], rc[NT][2];
+    load(wave, ra);
+    load(wave + kGuWaves, rb);
+    load(wave + 2 * kGuWaves, rc);
+#pragma unroll 1
+    for (int64_t i = wave; i < n; i += 3 * kGuWaves) {
+      mult(i, ra);
+      load(i + 3 * kGuWaves, ra);
+      mult(i + kGuWaves, rb);
+      load(i + 4 * kGuWaves, rb);
+      mult(i + 2 * kGuWaves, rc);
+      load(i + 5 * kGuWaves, rc);
+    }
+    // one wave after the other (LDS float atomics took twice the kernel's time);
+    // unrolled, so that the first wave's stores read nothing
+#pragma unroll
+    for (int w = 0; w < kGuWaves; ++w) {
+      if (w < n) {  // the waves that had a unit
+        if (w == wave) {
+#pragma unroll
+          for (int p = 0; p < NP; ++p)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) sum[p][r][lane] = w == 0 ? acc[p][r] : sum[p][r][lane] + acc[p][r];
+        }
+        __syncthreads();
+      }
+    }
+    for (int p = wave; p < NP; p += kGuWaves) {
+      int I = 0, J = p;
+      while (J >= NT - I) {
+        J -= NT - I;
+        ++I;
+      }
+      v16f v;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) v[r] = sum[p][r][lane];
+      flush_slot<32>(v, I, I + J, cacc + l * E * E, E, lane, pair64);
+    }
+    __syncthreads();  // the sums are read before the next segment's
+    t += n;
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -448,21 +563,31 @@ hipError_t launch_gram_mfma(const u64* bits, int64_t W, int64_t ld, int32_t E, i
     return hipGetLastError();
   }
   if (ld != sig_words(W)) return hipErrorInvalidValue;
-  // about as many blocks as fit on the GPU at once (two per CU up to 128
-  // experts, one at 256 where the kernel takes 208 VGPRs), each below the
-  // exact-count limit; every block flushes its counts with atomics at its end
-  const int64_t per_cu = E <= 128 ? 2 : 1;
-  int64_t bpl = std::max<int64_t>(1, ((int64_t)di.cu_count * per_cu + L - 1) / L);
+  const bool pair64 = (E & 1) == 0 && (reinterpret_cast<uintptr_t>(cacc) & 7) == 0;
+  if (E <= 96 || (E <= 128 && (int64_t)L * nch >= di.cu_count)) {
+    // one wave per SIMD keeps the matrix cores busy with three or four tiles;
+    // below that the loads of two are needed to keep the memory busy
+    const int64_t per_cu = E <= 64 ? 2 : 1;
+    const dim3 grid((unsigned)std::min<int64_t>(di.cu_count * per_cu, (int64_t)L * nch));
+    const dim3 block(kGuWaves * kWave);
+    switch ((E + 31) / 32) {
+      case 1: hipLaunchKernelGGL(k_gram_units<1>, grid, block, 0, s, bits, W, E, L, cacc, pair64); break;
+      case 2: hipLaunchKernelGGL(k_gram_units<2>, grid, block, 0, s, bits, W, E, L, cacc, pair64); break;
+      case 3: hipLaunchKernelGGL(k_gram_units<3>, grid, block, 0, s, bits, W, E, L, cacc, pair64); break;
+      default: hipLaunchKernelGGL(k_gram_units<4>, grid, block, 0, s, bits, W, E, L, cacc, pair64); break;
+    }
+    return hipGetLastError();
+  }
+  // fewer units than CUs of 97 to 128 experts (8 units: 18.3 us, k_gram_units 22.9
+  // us), and more than 128 experts: one block per CU and layer share (the kernel
+  // takes 208 VGPRs at 256), each below the exact-count limit; every block flushes
+  // its counts with atomics at its end
+  int64_t bpl = std::max<int64_t>(1, ((int64_t)di.cu_count + L - 1) / L);
   bpl = std::max<int64_t>(bpl, (nch + kGramMaxChunks - 1) / kGramMaxChunks);
   bpl = std::min<int64_t>(bpl, nch);
   if ((int64_t)L * bpl > 0x7FFFFFFF) return hipErrorInvalidValue;
-  const bool pair64 = (E & 1) == 0 && (reinterpret_cast<uintptr_t>(cacc) & 7) == 0;
   const dim3 grid((unsigned)(L * bpl));
-  if (E <= 32)
-    hipLaunchKernelGGL(k_gram_mfma<32>, grid, dim3(kFusedThreads), 0, s, bits, W, E, L, (int)bpl, cacc, pair64);
-  else if (E <= 64)
-    hipLaunchKernelGGL(k_gram_mfma<64>, grid, dim3(kFusedThreads), 0, s, bits, W, E, L, (int)bpl, cacc, pair64);
-  else if (E <= 128)
+  if (E <= 128)
     hipLaunchKernelGGL(k_gram_mfma<128>, grid, dim3(kFusedThreads), 0, s, bits, W, E, L, (int)bpl, cacc, pair64);
   else
     hipLaunchKernelGGL(k_gram_mfma<256>, grid, dim3(kFusedThreads), 0, s, bits, W, E, L, (int)bpl, cacc, pair64);
