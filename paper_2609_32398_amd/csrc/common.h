@@ -121,6 +121,7 @@ bool set_option(int opt, int value);
 
 // Zeroes the accumulators D [L][E][E] and, when out is given, the records that
 // launch_finalize accumulates into.
+hipError_t launch_clear_words(uint32_t* p, int64_t n, u64* rec, int64_t nrec, hipStream_t s);  // n words, nrec records' words
 hipError_t launch_clear(uint32_t* D, do_loss_result* out, int32_t E, int32_t L, hipStream_t s);
 
 // D holds the co-occurrence counts (upper triangle) and becomes

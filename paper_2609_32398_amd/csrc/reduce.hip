@@ -660,10 +660,14 @@ hipError_t launch_gram_bits(const u64* bits, int64_t W, int64_t ld, int32_t E, i
 }
 
 hipError_t launch_clear(uint32_t* D, do_loss_result* out, int32_t E, int32_t L, hipStream_t s) {
-  const int64_t n = (int64_t)L * E * E, nrec = out != nullptr ? (int64_t)L * (sizeof(do_loss_result) / 8) : 0;
+  return launch_clear_words(D, (int64_t)L * E * E, reinterpret_cast<u64*>(out),
+                            out != nullptr ? (int64_t)L * (sizeof(do_loss_result) / 8) : 0, s);
+}
+
+hipError_t launch_clear_words(uint32_t* p, int64_t n, u64* rec, int64_t nrec, hipStream_t s) {
   const int64_t work = std::max<int64_t>((n >> 2) + 1, nrec);
   const int64_t blocks = std::min<int64_t>((work + 255) / 256, 4096);
-  hipLaunchKernelGGL(k_clear, dim3((unsigned)blocks), dim3(256), 0, s, D, n, reinterpret_cast<u64*>(out), nrec);
+  hipLaunchKernelGGL(k_clear, dim3((unsigned)blocks), dim3(256), 0, s, p, n, rec, nrec);
   return hipGetLastError();
 }
 
