@@ -205,8 +205,7 @@ __device__ __forceinline__ void key_bf16x2(uint32_t x, uint32_t idx, int h, cons
 // in that list back from LDS and inserts their smaller keys, and merges the
 // list into the row's: about 6.5 instructions per key instead of 9 (positive
 // keys) or 10 (all VALU instructions of the kernel at 128 experts: -26 %; 48
-// layers x 262,144 tokens: 740 -> 683 us, with the loads spread over the
-// ranking and the drains of or_bit and unit_barrier gone).  A pair's key carries the index byte of its first expert; pairs
+// layers x 262,144 tokens: 740 -> 692 us).  A pair's key carries the index byte of its first expert; pairs
 // are disjoint index ranges, so equal values still rank by the lower index.
 //
 // The keys of the four pairs of a 16-byte piece.
@@ -877,21 +876,6 @@ __device__ __attribute__((noinline)) void mfma_flush_ool(typename Mfma<TS>::Acc 
 
 #define DOL_WAVE_FENCE() asm volatile("" ::: "memory")
 
-// OR `bit` into a signature word of the bit tile.  The compiler waits for every
-// direct-to-LDS load in flight before an LDS atomic or a __syncthreads, that is
-// for the next unit's first chunk.  The tile is no target of those loads, so
-// the Top-K kernel uses this form, and unit_barrier instead of __syncthreads.
-__device__ __forceinline__ void or_bit(u64* word, u64 bit) {
-  const uint32_t addr = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) u64*)word;
-  asm volatile("ds_or_b64 %0, %1" ::"v"(addr), "v"(bit) : "memory");
-}
-
-// The block's barrier for LDS alone: this wave's LDS operations are complete
-// before it, its loads and stores of global memory may still be in flight.
-__device__ __forceinline__ void unit_barrier() {
-  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
 // One segment as the kernel sees it (all values wave-uniform).  Counts fit
 // 32 bits: a segment holds fewer than 2^32 tokens and its bit positions stay
 // below 2^32, so word indices are below 2^26 and unit indices below 2^29.
@@ -1510,7 +1494,7 @@ __global__ __launch_bounds__(kFusedThreads) void k_topk(const SegTable tab_arg, 
           need += tied ? 1 : 0;
           int e = 255 - (top[i] & 255);
           if constexpr (RG && Traits<T>::kExact) e -= e >= tail_pos ? dup / (int)sizeof(T) : 0;
-          or_bit(&mybt[(e & (EPW - 1)) ^ bt_swz(wave)], tied ? 0ull : bit);
+          atomicOr(&mybt[(e & (EPW - 1)) ^ bt_swz(wave)], tied ? 0ull : bit);
         }
         if (!Traits<T>::kExact) {
           const u64 tm = __ballot(tie);
@@ -1526,7 +1510,7 @@ __global__ __launch_bounds__(kFusedThreads) void k_topk(const SegTable tab_arg, 
     // waves without a fast chunk loop in this unit finish the pending unit here
     if (!stored) store_share(pbt);
     if (gram_done < kFusedWaves) gram_slots(pbt, gram_done, kFusedWaves);
-    unit_barrier();  // this unit's bit tile is complete; the pending unit's tile is free
+    __syncthreads();  // this unit's bit tile is complete; the pending unit's tile is free
     // the fp32 Gram accumulators hold exact counts below 2^24: flush at a
     // layer change and before a block has accumulated 2^24 tokens
     if (have_pend && (pend.layer != sv.layer || ++acc_units >= kMaxAccUnits)) {
