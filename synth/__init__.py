@@ -35,13 +35,21 @@ WORKLOADS = {
 
 
 def build(force: bool = True) -> str:
-    """Compile gen.c into libsynth.so (gcc, OpenMP, portable x86-64 flags)."""
+    """Compile gen.c into libsynth.so (gcc, OpenMP, portable x86-64 flags).
+
+    Linked without -ffast-math: with it, gcc adds a start-up object that turns
+    denormals off in the thread that loads the library and in every thread that
+    one starts later, and the oracle would tie 1e-40 with zero.
+    """
     global _lib
     if not force and os.path.exists(_LIB_PATH):
         return _LIB_PATH
     tmp = _LIB_PATH + ".tmp"
-    cmd = ["gcc", "-O3", "-ffast-math", "-mavx2", "-mfma", "-fPIC", "-shared", "-fopenmp", "-std=c11", _SRC, "-o", tmp, "-lm"]
-    subprocess.run(cmd, check=True)
+    obj = _LIB_PATH + ".o"
+    subprocess.run(["gcc", "-O3", "-ffast-math", "-mavx2", "-mfma", "-fPIC", "-fopenmp", "-std=c11", "-c", _SRC, "-o", obj],
+                   check=True)
+    subprocess.run(["gcc", "-shared", "-fopenmp", obj, "-o", tmp, "-lm"], check=True)
+    os.remove(obj)
     os.replace(tmp, _LIB_PATH)
     _lib = None
     return _LIB_PATH

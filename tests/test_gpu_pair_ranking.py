@@ -24,14 +24,6 @@ def dl():
     return p
 
 
-def _chosen(orc, x: np.ndarray, k: int) -> np.ndarray:
-    """The oracle with denormals on: the score generator's library, built with
-    -ffast-math, makes the thread that loads it treat them as zeros (and with
-    that the oracle ties them: 8 of 320 words at 32 experts, k = 8)."""
-    torch.set_flush_denormal(False)
-    return orc.topk_signature(x, k, 1)
-
-
 def _bf16(x: np.ndarray) -> np.ndarray:
     return torch.from_numpy(x).to(torch.bfloat16).view(torch.int16).numpy().view(np.uint16).copy()
 
@@ -64,7 +56,7 @@ def test_pair_ranking(dl, orc, E, kind):
         x = _scores(kind, N, E)
         bits, D, _ = dl.do_fused(to_dev(x), k, want_bits=True)
         torch.cuda.synchronize()
-        F = _chosen(orc, x, k)
+        F = orc.topk_signature(x, k)
         np.testing.assert_array_equal(bits_np(bits, N)[0], orc.pack(F))
         np.testing.assert_array_equal(D_np(D)[0], orc.hamming(F))
 
@@ -78,7 +70,7 @@ def test_one_chunk_fp32_rows(dl, orc, E, k):
         print(f"[case] one chunk fp32 E={E} k={k} {kind}", flush=True)
         bits, D, _ = dl.do_fused(to_dev(x), k, want_bits=True)
         torch.cuda.synchronize()
-        F = _chosen(orc, x, k)
+        F = orc.topk_signature(x, k)
         np.testing.assert_array_equal(bits_np(bits, 577)[0], orc.pack(F))
         np.testing.assert_array_equal(D_np(D)[0], orc.hamming(F))
 
@@ -94,7 +86,7 @@ def test_layer_partitions(dl, orc, L, N):
     torch.cuda.synchronize()
     got, dist = bits_np(bits, N), D_np(D)
     for l in {0, 1, L // 2, L - 1}:
-        F = _chosen(orc, x[l], k)
+        F = orc.topk_signature(x[l], k)
         np.testing.assert_array_equal(got[l], orc.pack(F))
         np.testing.assert_array_equal(dist[l], orc.hamming(F))
     for l in range(2, L):  # the other layers repeat the first ones
