@@ -163,10 +163,12 @@ def _scores_3d(scores: torch.Tensor, name: str = "scores"):
 
 def _int32_array(values, n: int):
     """`values` as a host int32 array for the length of the call."""
-    try:  # 3 us for 256 Python ints; int() on each takes 20 us
-        return (ctypes.c_int32 * n).from_buffer(array.array("i", values))
-    except (TypeError, OverflowError):  # values that only int() converts
-        return (ctypes.c_int32 * n)(*[int(v) for v in values])
+    if isinstance(values, (list, tuple)):  # array would take bytes as raw memory
+        try:  # 3 us for 256 Python ints; int() on each takes 20 us
+            return (ctypes.c_int32 * n).from_buffer(array.array("i", values))
+        except Exception:  # values that only int() converts, or that it refuses in its own way
+            pass
+    return (ctypes.c_int32 * n)(*[int(v) for v in values])
 
 
 def _units(N: int) -> int:
