@@ -30,7 +30,8 @@ HBM_PEAK_GBS = 8000.0  # MI355X HBM3E, published
 
 # Sources whose hash identifies the score-streaming kernel; HBM byte counts
 # recorded under profiles/ are reported only while they still match.
-KERNEL_SOURCES = ["paper_2609_32398_amd/csrc/topk_kernel.h", "paper_2609_32398_amd/csrc/topk.hip", "paper_2609_32398_amd/csrc/common.h",
+KERNEL_SOURCES = ["paper_2609_32398_amd/csrc/topk_kernel.h", "paper_2609_32398_amd/csrc/schedule.h",
+                  "paper_2609_32398_amd/csrc/topk.hip", "paper_2609_32398_amd/csrc/common.h",
                   "paper_2609_32398_amd/hipbuild.py"]
 
 

@@ -47,15 +47,9 @@
 #include <hip/hip_ext.h>
 
 #include "common.h"
+#include "schedule.h"
 
 namespace dol {
-
-// Unit schedule of the Top-K kernel: groups of gu consecutive units (gu = 0:
-// one contiguous range per block), in 2^lp partitions (lp = 3: one per XCD).
-struct Sched {
-  int64_t gu;
-  int lp;
-};
 
 namespace {
 
@@ -929,9 +923,9 @@ __device__ __forceinline__ const unsigned char* word_rows(const Seg& sg, uint32_
 // Top-K (+ Gram) kernel.  Work unit: 8 consecutive signature words (512
 // output positions) of one segment, starting 8-aligned within it; one unit
 // per block step, one word (64 tokens) per wave.  The grid is persistent
-// (one block per CU slot); each block walks the units of its schedule: either
-// one contiguous range, or interleaved groups of consecutive units (see
-// next_unit and launch_one).
+// (one block per CU slot); each block walks the units of its schedule
+// (schedule.h): either one contiguous range, or interleaved groups of
+// consecutive units.
 //
 // Software pipeline: the signature stores and the Gram of a unit run during
 // the next unit (stores right after its first chunk arrives, one Gram slot
@@ -990,43 +984,11 @@ __global__ __launch_bounds__(kFusedThreads) void k_topk(const SegTable tab_arg, 
   const int lg = CB == 128 && rowB > 64 ? 3 : rowB > 32 ? 2 : rowB > 16 ? 1 : 0;
   const int dup = (16 - (rowB & 15)) & 15;
 
-  // Unit schedule: the unit range [lo, hi) of a block's partition is cut into
-  // groups of `gu` consecutive units, and the Gs blocks of the partition take
-  // groups pos, pos + Gs, pos + 2 Gs, ...  Contiguous ranges are the case of
-  // one group per block.  the flags above bit 0 select the partitions
-  // (2^lp of them, lp when the grid divides evenly, else 0):
-  //   0: one partition [0, U), pos = b
-  //   3: eight partitions, one per XCD (blocks are dispatched round-robin,
-  //      so block b runs on XCD b mod 8), of U/8 units each; the XCD's
-  //      blocks work on adjacent groups of its partition, so their signature
-  //      stores land side by side while each block stays in few layers (few
-  //      Gram flushes, and those of different XCDs go to different layers)
-  //   4, 5: two or four partitions per XCD, for 16 or 32 layers and more: each
-  //      block works in fewer layers still.  48 layers x 262,144 tokens, 128
-  //      experts: 690 us with 8 partitions (six flushes per block, 8 % of the
-  //      time), 649 us with 16, 636 us with 32.
-  // All unit counts are below 2^29 (64 segments of fewer than 2^32 tokens).
+  // this block's units (schedule.h); the launch made the grid a multiple of the partitions
   const uint32_t U = (uint32_t)tab->tile_start[tab->nseg];
-  const uint32_t G = gridDim.x;
-  const uint32_t b = blockIdx.x;
-  const int lp = (G & ((1u << (flags >> 1)) - 1)) == 0 ? flags >> 1 : 0;
-  const uint32_t part = b & ((1u << lp) - 1);
-  const uint32_t lo = (uint32_t)(((uint64_t)part * U) >> lp);
-  const uint32_t hi = (uint32_t)(((uint64_t)(part + 1) * U) >> lp);
-  const uint32_t Gs = G >> lp;
-  const uint32_t pos = b >> lp;
-  const uint32_t ug = lo + pos * gu;
-  if (ug >= hi) return;
-  // The unit after u in this block's schedule (U when there is none), from
-  // the bounds of the current group: called once per unit, in order.
-  uint32_t g_start = ug, g_end = min(ug + gu, hi);
-  auto next_unit = [&](uint32_t u_) -> uint32_t {
-    if (u_ + 1 < g_end) return u_ + 1;
-    g_start += Gs * gu;
-    if (g_start >= hi) return U;
-    g_end = min(g_start + gu, hi);
-    return g_start;
-  };
+  UnitWalk walk(U, gridDim.x, blockIdx.x, flags >> 1, gu);
+  const uint32_t ug = walk.first();
+  if (ug >= U) return;
 
   PopcGram<EPW, kFusedThreads, GM == kGramPopc> pg;
   if (GM == kGramPopc) pg.init(tid, E);
@@ -1323,7 +1285,7 @@ __global__ __launch_bounds__(kFusedThreads) void k_topk(const SegTable tab_arg, 
     const uint32_t wl = tl0 + wave;                      // this wave's local word
     const int cnt = AL ? kFusedWaves : (int)min((uint32_t)kFusedWaves, sv.words - tl0);  // words in this unit
     // next unit and its segment (wave-uniform)
-    const uint32_t un = next_unit(u);
+    const uint32_t un = walk.next(u);
     int seg_n = seg;
     Seg svn = sv;
     uint32_t tl0n = tl0 + 8;
@@ -1553,17 +1515,13 @@ hipError_t launch_one(const SegTable& tab, const PathArgs& a, bool fast, Sched s
   const int64_t units = tab.tile_start[tab.nseg];
   int64_t blocks = std::min<int64_t>((int64_t)di.cu_count * occ, units);
   blocks = std::max<int64_t>(blocks, 1);
-  int64_t gu = sc.gu;
-  const int64_t parts = int64_t(1) << sc.lp;
-  const int64_t per_part = (units + parts - 1) / parts;
-  const int64_t gs = std::max<int64_t>(blocks / parts, 1);
-  if (gu <= 0 || gu * gs > per_part) gu = (per_part + gs - 1) / gs;  // contiguous ranges
+  sc = plan_units(units, blocks, sc);
   const int flags = (fast ? 1 : 0) | (sc.lp << 1);
   if (pe.start != nullptr || pe.stop != nullptr)  // caller's timing events bound to this dispatch
     hipExtLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kFusedThreads), lds, s, pe.start, pe.stop, 0u, tab, a,
-                          flags, (uint32_t)gu);
+                          flags, (uint32_t)sc.gu);
   else
-    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kFusedThreads), lds, s, tab, a, flags, (uint32_t)gu);
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kFusedThreads), lds, s, tab, a, flags, (uint32_t)sc.gu);
   return hipGetLastError();
 }
 
