@@ -509,7 +509,12 @@ hipError_t launch_topk(do_dtype dt, SegTable& tab, int nseg, const PathArgs& a, 
   // the in-register ranking needs rows of at least one 16-byte piece
   const int rowB = a.E * (dt == DO_F32 ? 4 : 2);
   const bool fast = rowB >= 16 && a.k <= kFastMaxK && a.E <= kFastMaxE;
-  const RowMode mode = !vec_rows || rowB % 128 != 0 || !fast ? kRagged : aligned_segments(tab) ? kAligned : kDirect;
+  // 16-byte aligned rows load straight into LDS at every length; kRagged, which
+  // takes them too, was 0 to 46 % slower than kPieces (see RowMode)
+  const RowMode mode = !vec_rows || !fast        ? kRagged
+                       : rowB % 128 != 0         ? kPieces
+                       : !aligned_segments(tab) ? kDirect
+                                                : kAligned;
   hipEvent_t ev[2] = {nullptr, nullptr};
   const int forced = g_opt_sched.load(std::memory_order_relaxed);
   Sched sc = forced >= 0 ? kSchedCand[forced] : tuned_schedule(dt, tab, a, mode, fast, s, ev);
@@ -531,6 +536,7 @@ hipError_t launch_topk(do_dtype dt, SegTable& tab, int nseg, const PathArgs& a, 
     if (e != hipSuccess) return e;
   }
   const hipError_t e = mode == kRagged ? launch_ragged(dt, gram_mode(), tab, a, fast, sc, s, use)
+                       : mode == kPieces ? launch_pieces(dt, gram_mode(), tab, a, sc, s, use)
                        : dt == DO_F32  ? launch_ep<float>(mode, tab, a, sc, s, use)
                                        : launch_ep<uint16_t>(mode, tab, a, sc, s, use);
   if (e != hipSuccess || !around) return e;

@@ -383,20 +383,19 @@ __device__ __forceinline__ uint32_t idx_bytes(int e0) { return 0xFCFDFEFFu - 0x0
 // reading their rows' piece q then touch all 64 banks once.
 __device__ __forceinline__ int stage_swz(int r, int lg) { return (r >> (4 - lg)) & ((1 << lg) - 1); }
 
-// Rank the first nv pieces of a staged chunk; the piece `tail_q` (-1: none) is
-// the row's last 16 bytes, of which the first `dup` bytes repeat elements of
-// the piece before it: they are set to all ones (a NaN, ranked last and never
-// selected on the fast path), and its experts are E - kVec ... E - 1.  The
+// Rank the first nv pieces of a staged chunk of at most NP: piece q of the lane's
+// row at row + (16 q ^ sw).  The piece `tail_q` (-1: none) is the row's last 16
+// bytes, of which the first `dup` bytes repeat elements of the piece before it:
+// they are set to all ones (a NaN, ranked last and never selected on the fast
+// path), and its experts are E - kVec ... E - 1.  The
 // index byte of an fp32 key is 255 - expert, that of a bf16 key 255 - position
 // in the staged pieces (the selection takes dup / 2 off the tail's positions).
 // bf16 chunks of at least kPairPieces pieces are ranked by pairs: at three
 // pieces the second half's 24 insertions just pay for reading the pairs back.
 constexpr int kPairPieces = 4;
-template <typename T, bool GEN, int kPieces>
-__device__ __forceinline__ void rank_staged(unsigned char* sbuf, int lane, int lg, int cv0, int nv, int tail_q,
-                                            int dup, int E, const KeySel& ks, int (&top)[8], int& rej) {
-  unsigned char* row = sbuf + (lane << (4 + lg));
-  const int sw = stage_swz(lane, lg) << 4;
+template <typename T, bool GEN, int NP>
+__device__ __forceinline__ void rank_staged(unsigned char* row, int sw, int cv0, int nv, int tail_q, int dup, int E,
+                                            const KeySel& ks, int (&top)[8], int& rej) {
   constexpr int kV = Traits<T>::kVec;
   // the next piece is read while the current one is ranked (unconditionally: a
   // piece past nv re-reads the last one)
@@ -408,7 +407,7 @@ __device__ __forceinline__ void rank_staged(unsigned char* sbuf, int lane, int l
       x[i] |= b >= 4 ? ~0u : b == 2 ? 0xFFFFu : 0u;
     }
   };
-  if (Traits<T>::kExact && kPieces == 8 && nv >= kPairPieces) {
+  if (Traits<T>::kExact && NP == 8 && nv >= kPairPieces) {
     if (tail_q >= 0) {  // in the stage buffer too: resolve_pairs reads it again
       v4u x = piece(tail_q);
       void_dup(x);
@@ -419,7 +418,7 @@ __device__ __forceinline__ void rank_staged(unsigned char* sbuf, int lane, int l
     for (int i = 0; i < 8; ++i) fr[i] = INT_MIN;
     v4u xn = piece(0);
 #pragma unroll
-    for (int q = 0; q < kPieces; ++q) {
+    for (int q = 0; q < NP; ++q) {
       if (q >= nv) break;  // wave-uniform
       const v4u x = xn;
       xn = piece(q + 1);
@@ -429,13 +428,13 @@ __device__ __forceinline__ void rank_staged(unsigned char* sbuf, int lane, int l
 #pragma unroll
       for (int i = 0; i < 4; ++i) insert_pair(fr, g[i], 4 * q + i);
     }
-    resolve_pairs<GEN>(fr, row, (uint32_t)sw, 16 * kPieces);
+    resolve_pairs<GEN>(fr, row, (uint32_t)sw, 16 * NP);
     merge8(top, fr, cv0 == 0);
     return;
   }
   v4u xn = piece(0);
 #pragma unroll
-  for (int q = 0; q < kPieces; ++q) {
+  for (int q = 0; q < NP; ++q) {
     if (q >= nv) break;  // wave-uniform
     v4u x = xn;
     xn = piece(q + 1);
@@ -943,12 +942,18 @@ __device__ __forceinline__ const unsigned char* word_rows(const Seg& sg, uint32_
 //             (Bound by the VALU.  100 bf16 experts, 4 x 100,003 tokens: 187 us
 //             with every lane reading its own row, 59 us this way.)
 //   kDirect:  16-byte aligned rows of whole 128-byte chunks: direct-to-LDS loads.
+//   kPieces:  16-byte aligned rows of whole 16-byte pieces, the last chunk
+//             partial: kDirect, where the lanes of a missing piece load the
+//             row's last piece again and only the pieces there are are ranked.
+//             (do_topk_signature of 4 x 262,144 tokens through kRagged and this
+//             way: bf16, 40 experts 39.1 and 35.7 us, 88: 68 and 62, 200: 194
+//             and 134; fp32, 24: 43 and 39, 100: 137 and 134, 152: 244 and 167.)
 //   kAligned: kDirect, and every segment starts and ends on a unit boundary
 //             (token offset and count multiples of 512), so every word is
 //             full, every unit has 8 words, no word is shared between
 //             segments and every row of a chunk lies inside its segment.  The
 //             edge handling then compiles away, with the registers it holds.
-enum RowMode { kRagged = 0, kDirect = 1, kAligned = 2 };
+enum RowMode { kRagged = 0, kDirect = 1, kAligned = 2, kPieces = 3 };
 
 // Stage buffers of a block: two per wave, one for kRagged (its next chunk waits in registers).
 template <int MODE>
@@ -960,6 +965,7 @@ template <typename T, int EP, int GM, int MODE>
 __global__ __launch_bounds__(kFusedThreads) void k_topk(const SegTable tab_arg, const PathArgs a, int flags, uint32_t gu) {
   constexpr bool AL = MODE == kAligned;
   constexpr bool RG = MODE == kRagged;
+  constexpr bool PC = MODE == kPieces;
   (void)tab_arg;  // read through `tab` below (it is the first kernel argument)
   const SegTablePtr tab = (SegTablePtr)__builtin_amdgcn_kernarg_segment_ptr();
   constexpr int EPW = EP < 32 ? 32 : EP;  // signature words per slot of the bit tile
@@ -976,7 +982,7 @@ __global__ __launch_bounds__(kFusedThreads) void k_topk(const SegTable tab_arg, 
   // bytes of a row per chunk (kRagged at 256 experts: half chunks, whose prefetch
   // takes 16 VGPRs instead of 32; with 32 the kernel spilled)
   constexpr int CB = RG && EPW > 128 ? 64 : 128;
-  constexpr int kPieces = CB / 16;
+  constexpr int kChunkPieces = CB / 16;
   const int nch = (rowB + CB - 1) / CB;
   unsigned char* st = smem + wave * (stage_bytes<MODE>() / kFusedWaves);  // this wave's two stage buffers (kRagged: one)
   // kRagged: log2 of the 16-byte slots a row takes in the stage buffer, and the
@@ -1049,7 +1055,20 @@ __global__ __launch_bounds__(kFusedThreads) void k_topk(const SegTable tab_arg, 
   // instruction.
   auto dma = [&](const Seg& sg, uint32_t wl, int c_, unsigned char* sbuf) {
     const unsigned char* cbase = word_rows(sg, wl, rowB) + c_ * 128;  // row 0 of the chunk (uniform)
-    if (AL || (wl >= sg.full_lo && wl < sg.full_hi)) {  // every row inside the segment
+    if (PC && c_ + 1 == nch) {  // the row's last, partial chunk
+      const int nv = (rowB - 128 * c_) >> 4;
+      const uint32_t p_even = (uint32_t)((lane >> 3) * rowB + min(q_even, nv - 1) * 16);
+      const uint32_t p_odd = (uint32_t)((lane >> 3) * rowB + min(q_even ^ 1, nv - 1) * 16);
+      int r_lo, r_hi;
+      row_bounds(sg, wl, r_lo, r_hi);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int r = 8 * j + row_in_j0;
+        if (r >= r_lo && r < r_hi)
+          __builtin_amdgcn_global_load_lds(cbase + (uint32_t)(j * 8 * rowB) + ((j & 1) ? p_odd : p_even),
+                                           (__attribute__((address_space(3))) void*)(sbuf + j * 1024), 16, 0, kStreamPolicy);
+      }
+    } else if (AL || (wl >= sg.full_lo && wl < sg.full_hi)) {  // every row inside the segment
 #pragma unroll
       for (int j = 0; j < 8; ++j) dma_row8(cbase, j, sbuf);
     } else {
@@ -1068,7 +1087,7 @@ __global__ __launch_bounds__(kFusedThreads) void k_topk(const SegTable tab_arg, 
   // 64 j + lane of the stage buffer.  Every load is issued unconditionally
   // (positions without a token or a piece of their own re-read a valid one,
   // whose values are never used), so that none waits for another.
-  v4u pre[kPieces];
+  v4u pre[kChunkPieces];
   auto fetch = [&](const Seg& sg, uint32_t wl, int c_) __attribute__((always_inline)) {
     const int nv = (min(CB, rowB - CB * c_) + 15) >> 4;
     const int row_in = lane >> lg, slot = lane & ((1 << lg) - 1);
@@ -1081,7 +1100,7 @@ __global__ __launch_bounds__(kFusedThreads) void k_topk(const SegTable tab_arg, 
     if (wl >= sg.full_lo && wl < sg.full_hi) {
       const uint32_t ro = (uint32_t)(row_in * rowB);
 #pragma unroll
-      for (int j = 0; j < kPieces; ++j)
+      for (int j = 0; j < kChunkPieces; ++j)
         if (j < (1 << lg))
           pre[j] = __builtin_nontemporal_load(
               reinterpret_cast<const v4u_any*>(wbase + (uint32_t)(j * rstep * rowB) + (ro + ((j & 1) ? p1 : p0))));
@@ -1089,7 +1108,7 @@ __global__ __launch_bounds__(kFusedThreads) void k_topk(const SegTable tab_arg, 
       int r_lo, r_hi;
       row_bounds(sg, wl, r_lo, r_hi);
 #pragma unroll
-      for (int j = 0; j < kPieces; ++j)
+      for (int j = 0; j < kChunkPieces; ++j)
         if (j < (1 << lg)) {
           const int r = min(max(row_in + j * rstep, r_lo), r_hi - 1);
           pre[j] = __builtin_nontemporal_load(
@@ -1099,7 +1118,7 @@ __global__ __launch_bounds__(kFusedThreads) void k_topk(const SegTable tab_arg, 
   };
   auto stage = [&](unsigned char* sbuf) __attribute__((always_inline)) {
 #pragma unroll
-    for (int j = 0; j < kPieces; ++j)
+    for (int j = 0; j < kChunkPieces; ++j)
       if (j < (1 << lg)) *reinterpret_cast<v4u*>(sbuf + j * 1024 + lane * 16) = pre[j];
   };
   // starts the loads of chunk c_ of a word (kRagged: into registers; else into sbuf)
@@ -1374,10 +1393,18 @@ __global__ __launch_bounds__(kFusedThreads) void k_topk(const SegTable tab_arg, 
             if constexpr (RG) {
               const int nv = (min(CB, rowB - CB * c) + 15) >> 4;
               const int tail_q = dup != 0 && c + 1 == nch ? nv - 1 : -1;
+              unsigned char* row = cur + (lane << (4 + lg));
+              const int sw = stage_swz(lane, lg) << 4;
               if (gk)
-                rank_staged<T, true, kPieces>(cur, lane, lg, c * kPieces, nv, tail_q, dup, E, ks, top, rej);
+                rank_staged<T, true, kChunkPieces>(row, sw, c * kChunkPieces, nv, tail_q, dup, E, ks, top, rej);
               else
-                rank_staged<T, false, kPieces>(cur, lane, lg, c * kPieces, nv, tail_q, dup, E, ks, top, rej);
+                rank_staged<T, false, kChunkPieces>(row, sw, c * kChunkPieces, nv, tail_q, dup, E, ks, top, rej);
+            } else if (PC && c + 1 == nch) {
+              const int nv = (rowB - 128 * c) >> 4;
+              if (gk)
+                rank_staged<T, true, 8>(cur + lane * 128, row_swizzle(lane) << 4, c * 8, nv, -1, 0, E, ks, top, rej);
+              else
+                rank_staged<T, false, 8>(cur + lane * 128, row_swizzle(lane) << 4, c * 8, nv, -1, 0, E, ks, top, rej);
             } else {
               if (gk)
                 rank_chunk<T, true>(cur, lane, c * 8, ks, top, rej, issue);
@@ -1538,6 +1565,10 @@ hipError_t launch_mode(int gm, const SegTable& tab, const PathArgs& a, bool fast
 // More than 256 experts and k <= kWideMaxK, signatures only (topk_wide.hip).
 constexpr int kWideMaxK = 16;
 hipError_t launch_wide(do_dtype dt, const SegTable& tab, const PathArgs& a, hipStream_t s, const ProfEv& pe);
+
+// The launches of the kPieces rows (topk_pieces.hip).
+hipError_t launch_pieces(do_dtype dt, int gm, const SegTable& tab, const PathArgs& a, Sched sc, hipStream_t s,
+                         const ProfEv& pe);
 
 // The launches of the kRagged rows (topk_ragged.hip); gm: the Gram kind when a.cacc is given.
 hipError_t launch_ragged(do_dtype dt, int gm, const SegTable& tab, const PathArgs& a, bool fast, Sched sc,

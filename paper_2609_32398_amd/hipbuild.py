@@ -9,7 +9,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB_PATH = os.path.join(HERE, "libdoloss.so")
-SOURCES = ["api.hip", "topk.hip", "topk_ragged.hip", "topk_wide.hip", "reduce.hip", "surrogate.hip", "loadstats.hip", "rem.hip"]
+SOURCES = ["api.hip", "topk.hip", "topk_ragged.hip", "topk_pieces.hip", "topk_wide.hip", "reduce.hip", "surrogate.hip", "loadstats.hip", "rem.hip"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950",
