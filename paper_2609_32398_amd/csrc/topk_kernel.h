@@ -1279,6 +1279,23 @@ __global__ __launch_bounds__(kFusedThreads) void k_topk(const SegTable tab_arg, 
   // 4,096 tokens, where nearly every wave meets one: 21.5 -> 16.4 us); longer fp32 rows
   // look at their end, and those tokens are re-ranked exactly.
   bool gen = false;
+  // only these rows can be ranked again after their first chunk
+  constexpr bool kRankAgain = Traits<T>::kExact || EP == 32;
+  // kAligned: whether the next chunk's loads are spread over the ranking of the
+  // current one (below).  bf16 rows and rows of one chunk gain (fp32, 32 experts,
+  // 4 x 262,144 tokens, do_topk_signature: 35.1 us issued together, 33.3 spread).
+  // Of the longer fp32 rows only those of 512 and 1,024 bytes do, whose rows all
+  // start on the same few HBM channels, and only over many units (128 experts:
+  // 104 -> 98 us at 8 units per block, 24.3 -> 25.2 at two; 256: 680 -> 673 at 32,
+  // 165 -> 169 at 8).  The others lose 2 to 5 % (64 experts: 59.6 -> 61.0, 96: 70.9
+  // -> 72.6, 160: 106 -> 111), and 10 % where a block has one unit and nothing else
+  // hides the later loads.  With a Gram, 129 to 256 fp32 experts leave no registers
+  // for the choice (do_fused of 2 x 4,194,304 tokens, 256 experts: 1,420 us spread,
+  // 1,440 together, 1,449 chosen at run time; 4 x 262,144: 227 spread, 222 together).
+  constexpr bool kMustSpread = AL && (Traits<T>::kExact || EP == 32 || (EP == 256 && GM != kGramNone));
+  constexpr bool kMaySpread = AL && (kMustSpread || EP >= 128);
+  const bool spread =
+      kMaySpread && (kMustSpread || ((rowB & (rowB - 1)) == 0 && U > (EP == 128 ? 2 : 16) * gridDim.x));
   int cb = 0;  // stage buffer holding the current chunk
   // key byte selectors, opaque to the compiler so that they stay in VGPRs
   // instead of being rematerialised for every key
@@ -1364,20 +1381,21 @@ __global__ __launch_bounds__(kFusedThreads) void k_topk(const SegTable tab_arg, 
             DOL_WAIT_VMEM();  // this chunk's direct-to-LDS loads (and earlier stores) have completed
           DOL_WAVE_FENCE();
           unsigned char* other = st + (cb ^ 1) * kChunkBytes;
-          // kAligned: the eight loads of the next chunk are issued one after each
+          // `spread`: the eight loads of the next chunk are issued one after each
           // ranked piece.  Issued together they queued behind those of the other
           // waves and held up waves 4-7 for 18 % of their time.  After the block's
           // last chunk they read the current chunk once more, into a free buffer.
           const unsigned char* nrow = word_rows(sv, wl, rowB) + (c + 1 < nch ? c + 1 : c) * 128;
           if (c + 1 == nch && next_mine) nrow = word_rows(svn, wln, rowB);
           auto issue = [&](int v) __attribute__((always_inline)) {
-            if constexpr (AL) {
+            if constexpr (kMaySpread) {
+              if (!kMustSpread && !spread) return;
               __builtin_amdgcn_sched_barrier(0);
               dma_row8(nrow, v, other);
               __builtin_amdgcn_sched_barrier(0);
             }
           };
-          if constexpr (!AL) {
+          if (!kMustSpread && !spread) {
             if (c + 1 < nch)
               load_chunk(sv, wl, c + 1, other);
             else if (next_mine)
@@ -1411,7 +1429,7 @@ __global__ __launch_bounds__(kFusedThreads) void k_topk(const SegTable tab_arg, 
               else
                 rank_chunk<T, false>(cur, lane, c * 8, ks, top, rej, issue);
             }
-            if (gk || c > 0 || !(Traits<T>::kExact || nch == 1) ||
+            if (!kRankAgain || gk || c > 0 || !(Traits<T>::kExact || nch == 1) ||
                 __ballot(valid && kth_key(top, k) < Traits<T>::kPosMin) == 0ull)
               break;
             gen = gk = true;
