@@ -953,7 +953,14 @@ __device__ __forceinline__ const unsigned char* word_rows(const Seg& sg, uint32_
 //             full, every unit has 8 words, no word is shared between
 //             segments and every row of a chunk lies inside its segment.  The
 //             edge handling then compiles away, with the registers it holds.
-enum RowMode { kRagged = 0, kDirect = 1, kAligned = 2, kPieces = 3 };
+//   kTiny:    rows below 16 bytes: every lane selects from its own row in memory.
+//             Nothing is staged or ranked in registers, so two blocks fit a CU
+//             (do_topk_signature of 4 x 262,144 tokens, kRagged's per-lane path
+//             and this: 3 fp32 experts 27.7 and 18.6 us, 6 bf16 33.8 and 22.8).
+//             Rows of k > 8 stay with kRagged: a second block's rows would push
+//             the first's out of the caches (128 fp32 experts, k = 24: 11.1 ms,
+//             25.3 with two blocks per CU).
+enum RowMode { kRagged = 0, kDirect = 1, kAligned = 2, kPieces = 3, kTiny = 4 };
 
 // Stage buffers of a block: two per wave, one for kRagged (its next chunk waits in registers).
 template <int MODE>
@@ -972,7 +979,7 @@ __global__ __launch_bounds__(kFusedThreads) void k_topk(const SegTable tab_arg, 
   typedef GramShape<EPW> GS;
   typedef typename Mfma<GS::TS>::Acc Acc;
   extern __shared__ __align__(16) unsigned char smem[];
-  const bool fast = (flags & 1) != 0;
+  const bool fast = MODE != kTiny && (flags & 1) != 0;
   u64* bt_all = reinterpret_cast<u64*>(smem + (fast ? stage_bytes<MODE>() : 0));  // [2][kFusedWaves][EPW]
 
   const int tid = threadIdx.x, lane = tid & 63;

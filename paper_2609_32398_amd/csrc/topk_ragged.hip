@@ -1,5 +1,6 @@
 // The Top-K kernel (topk_kernel.h) for the kRagged rows: any row length and
-// alignment, and the shapes that only the exact per-lane selection takes.
+// alignment, and the shapes that only the exact per-lane selection takes (the
+// kTiny rows among them).
 #include "topk_kernel.h"
 
 namespace dol {
@@ -8,6 +9,7 @@ namespace {
 template <typename T>
 hipError_t launch_ep(int gm, const SegTable& tab, const PathArgs& a, bool fast, Sched sc, hipStream_t s,
                      const ProfEv& pe) {
+  if (a.E * (int)sizeof(T) < 16) return launch_mode<T, 32, kTiny>(gm, tab, a, false, sc, s, pe);
   if (a.E <= 32) return launch_mode<T, 32, kRagged>(gm, tab, a, fast, sc, s, pe);
   if (a.E <= 64) return launch_mode<T, 64, kRagged>(gm, tab, a, fast, sc, s, pe);
   if (a.E <= 128) return launch_mode<T, 128, kRagged>(gm, tab, a, fast, sc, s, pe);
