@@ -1367,116 +1367,134 @@ __global__ __launch_bounds__(kFusedThreads) void k_topk(const SegTable tab_arg, 
         int rej = INT_MIN;
 #pragma unroll
         for (int i = 0; i < 8; ++i) top[i] = INT_MIN;
-        bool gk = gen;  // key kind of the next chunk of this row
-        for (int c = 0; c < nch; ++c) {
-          unsigned char* cur = st + cb * kChunkBytes;
-          // Two waves share each SIMD and its arbiter prefers the older one:
-          // left to it, waves 0-3 end every unit early and wait at the block
-          // barrier (29 % of their time) while waves 4-7 finish alone.
-          // Waves 4-7 therefore take the higher priority for even chunks (bf16:
-          // after their share of the signature stores), which evens out when
-          // the two waves of a SIMD reach the barrier.
-          if (wave >= 4) {
-            if (c & 1)
-              __builtin_amdgcn_s_setprio(0);
-            else if constexpr (!Traits<T>::kExact)
-              __builtin_amdgcn_s_setprio(1);
-          }
-          if constexpr (RG)
-            stage(cur);  // waits for the chunk's loads
-          else
-            DOL_WAIT_VMEM();  // this chunk's direct-to-LDS loads (and earlier stores) have completed
-          DOL_WAVE_FENCE();
-          unsigned char* other = st + (cb ^ 1) * kChunkBytes;
-          // `spread`: the eight loads of the next chunk are issued one after each
-          // ranked piece.  Issued together they queued behind those of the other
-          // waves and held up waves 4-7 for 18 % of their time.  After the block's
-          // last chunk they read the current chunk once more, into a free buffer.
-          const unsigned char* nrow = word_rows(sv, wl, rowB) + (c + 1 < nch ? c + 1 : c) * 128;
-          if (c + 1 == nch && next_mine) nrow = word_rows(svn, wln, rowB);
-          auto issue = [&](int v) __attribute__((always_inline)) {
-            if constexpr (kMaySpread) {
-              if (!kMustSpread && !spread) return;
-              __builtin_amdgcn_sched_barrier(0);
-              dma_row8(nrow, v, other);
-              __builtin_amdgcn_sched_barrier(0);
+        int sk, sk1, ks_;
+        // kRagged, fp32 rows of several chunks: a row whose threshold is not
+        // positive is loaded and ranked once more with general keys, which the wave
+        // then keeps.  65,536 tokens of negative scores, do_topk_signature, with
+        // the exact per-lane selection after the first ranking and this way: 53
+        // experts 31 and 14 us, 150: 83 and 38.
+        for (;;) {
+          bool gk = gen;  // key kind of the next chunk of this row
+          for (int c = 0; c < nch; ++c) {
+            unsigned char* cur = st + cb * kChunkBytes;
+            // Two waves share each SIMD and its arbiter prefers the older one:
+            // left to it, waves 0-3 end every unit early and wait at the block
+            // barrier (29 % of their time) while waves 4-7 finish alone.
+            // Waves 4-7 therefore take the higher priority for even chunks (bf16:
+            // after their share of the signature stores), which evens out when
+            // the two waves of a SIMD reach the barrier.
+            if (wave >= 4) {
+              if (c & 1)
+                __builtin_amdgcn_s_setprio(0);
+              else if constexpr (!Traits<T>::kExact)
+                __builtin_amdgcn_s_setprio(1);
             }
-          };
-          if (!kMustSpread && !spread) {
-            if (c + 1 < nch)
-              load_chunk(sv, wl, c + 1, other);
-            else if (next_mine)
-              load_chunk(svn, wln, 0, other);
-          }
-          if (!stored) {
-            store_share(pbt);
-            stored = true;
-          }
-          if constexpr (Traits<T>::kExact)
-            if (wave >= 4 && !(c & 1)) __builtin_amdgcn_s_setprio(1);
-          for (;;) {
-            if constexpr (RG) {
-              const int nv = (min(CB, rowB - CB * c) + 15) >> 4;
-              const int tail_q = dup != 0 && c + 1 == nch ? nv - 1 : -1;
-              unsigned char* row = cur + (lane << (4 + lg));
-              const int sw = stage_swz(lane, lg) << 4;
-              if (gk)
-                rank_staged<T, true, kChunkPieces>(row, sw, c * kChunkPieces, nv, tail_q, dup, E, ks, top, rej);
-              else
-                rank_staged<T, false, kChunkPieces>(row, sw, c * kChunkPieces, nv, tail_q, dup, E, ks, top, rej);
-            } else if (PC && c + 1 == nch) {
-              const int nv = (rowB - 128 * c) >> 4;
-              if (gk)
-                rank_staged<T, true, 8>(cur + lane * 128, row_swizzle(lane) << 4, c * 8, nv, -1, 0, E, ks, top, rej);
-              else
-                rank_staged<T, false, 8>(cur + lane * 128, row_swizzle(lane) << 4, c * 8, nv, -1, 0, E, ks, top, rej);
-            } else {
-              if (gk)
-                rank_chunk<T, true>(cur, lane, c * 8, ks, top, rej, issue);
-              else
-                rank_chunk<T, false>(cur, lane, c * 8, ks, top, rej, issue);
+            if constexpr (RG)
+              stage(cur);  // waits for the chunk's loads
+            else
+              DOL_WAIT_VMEM();  // this chunk's direct-to-LDS loads (and earlier stores) have completed
+            DOL_WAVE_FENCE();
+            unsigned char* other = st + (cb ^ 1) * kChunkBytes;
+            // `spread`: the eight loads of the next chunk are issued one after each
+            // ranked piece.  Issued together they queued behind those of the other
+            // waves and held up waves 4-7 for 18 % of their time.  After the block's
+            // last chunk they read the current chunk once more, into a free buffer.
+            const unsigned char* nrow = word_rows(sv, wl, rowB) + (c + 1 < nch ? c + 1 : c) * 128;
+            if (c + 1 == nch && next_mine) nrow = word_rows(svn, wln, rowB);
+            auto issue = [&](int v) __attribute__((always_inline)) {
+              if constexpr (kMaySpread) {
+                if (!kMustSpread && !spread) return;
+                __builtin_amdgcn_sched_barrier(0);
+                dma_row8(nrow, v, other);
+                __builtin_amdgcn_sched_barrier(0);
+              }
+            };
+            if (!kMustSpread && !spread) {
+              if (c + 1 < nch)
+                load_chunk(sv, wl, c + 1, other);
+              else if (next_mine)
+                load_chunk(svn, wln, 0, other);
             }
-            if (!kRankAgain || gk || c > 0 || !(Traits<T>::kExact || nch == 1) ||
-                __ballot(valid && kth_key(top, k) < Traits<T>::kPosMin) == 0ull)
-              break;
-            gen = gk = true;
-            rej = INT_MIN;
+            if (!stored) {
+              store_share(pbt);
+              stored = true;
+            }
+            if constexpr (Traits<T>::kExact)
+              if (wave >= 4 && !(c & 1)) __builtin_amdgcn_s_setprio(1);
+            for (;;) {
+              if constexpr (RG) {
+                const int nv = (min(CB, rowB - CB * c) + 15) >> 4;
+                const int tail_q = dup != 0 && c + 1 == nch ? nv - 1 : -1;
+                unsigned char* row = cur + (lane << (4 + lg));
+                const int sw = stage_swz(lane, lg) << 4;
+                if (gk)
+                  rank_staged<T, true, kChunkPieces>(row, sw, c * kChunkPieces, nv, tail_q, dup, E, ks, top, rej);
+                else
+                  rank_staged<T, false, kChunkPieces>(row, sw, c * kChunkPieces, nv, tail_q, dup, E, ks, top, rej);
+              } else if (PC && c + 1 == nch) {
+                const int nv = (rowB - 128 * c) >> 4;
+                if (gk)
+                  rank_staged<T, true, 8>(cur + lane * 128, row_swizzle(lane) << 4, c * 8, nv, -1, 0, E, ks, top, rej);
+                else
+                  rank_staged<T, false, 8>(cur + lane * 128, row_swizzle(lane) << 4, c * 8, nv, -1, 0, E, ks, top, rej);
+              } else {
+                if (gk)
+                  rank_chunk<T, true>(cur, lane, c * 8, ks, top, rej, issue);
+                else
+                  rank_chunk<T, false>(cur, lane, c * 8, ks, top, rej, issue);
+              }
+              if (!kRankAgain || gk || c > 0 || !(Traits<T>::kExact || nch == 1) ||
+                  __ballot(valid && kth_key(top, k) < Traits<T>::kPosMin) == 0ull)
+                break;
+              gen = gk = true;
+              rej = INT_MIN;
+  #pragma unroll
+              for (int i = 0; i < 8; ++i) top[i] = INT_MIN;
+            }
+            // bf16: once the 8th key of every token of the wave is a positive
+            // number, the rest of the row takes positive keys.  A negative score
+            // then keys below zero instead of at its general key, below that 8th
+            // key either way, and positive scores key the same under both kinds,
+            // so the list ends exactly as with general keys throughout.
+            if (Traits<T>::kExact && gk && c + 1 < nch &&
+                __ballot(valid && top[7] < Traits<T>::kPosMin) == 0ull)
+              gk = false;
+            if (gram_done < kFusedWaves) {
+              const int s_end = (((c + 1) * kFusedWaves) / nch) & ~(kGramStep - 1);
+              gram_slots(pbt, gram_done, s_end);
+              gram_done = s_end;
+            }
+            DOL_WAVE_FENCE();
+            if constexpr (!RG) cb ^= 1;
+          }
+          if (wave >= 4) __builtin_amdgcn_s_setprio(0);
+          // the k-th and (k+1)-th keys: a wave-uniform branch on k, so that no
+          // per-position predicate on k stays live (in registers) across the loop
+          // (opaque: a comparison per position hoisted out of the unit loop takes
+          // two SGPRs each, which spilled)
+          ks_ = k;
+          asm volatile("" : "+s"(ks_));
+          switch (ks_) {
+            case 1: sk = top[0]; sk1 = top[1]; break;
+            case 2: sk = top[1]; sk1 = top[2]; break;
+            case 3: sk = top[2]; sk1 = top[3]; break;
+            case 4: sk = top[3]; sk1 = top[4]; break;
+            case 5: sk = top[4]; sk1 = top[5]; break;
+            case 6: sk = top[5]; sk1 = top[6]; break;
+            case 7: sk = top[6]; sk1 = top[7]; break;
+            default: sk = top[7]; sk1 = rej; break;
+          }
+          if constexpr (RG && !Traits<T>::kExact && EP > 32) {
+            if (!gen && __ballot(valid && sk < Traits<T>::kPosMin) != 0ull) {
+              gen = true;
+              rej = INT_MIN;
 #pragma unroll
-            for (int i = 0; i < 8; ++i) top[i] = INT_MIN;
+              for (int i = 0; i < 8; ++i) top[i] = INT_MIN;
+              load_chunk(sv, wl, 0, st);
+              continue;
+            }
           }
-          // bf16: once the 8th key of every token of the wave is a positive
-          // number, the rest of the row takes positive keys.  A negative score
-          // then keys below zero instead of at its general key, below that 8th
-          // key either way, and positive scores key the same under both kinds,
-          // so the list ends exactly as with general keys throughout.
-          if (Traits<T>::kExact && gk && c + 1 < nch &&
-              __ballot(valid && top[7] < Traits<T>::kPosMin) == 0ull)
-            gk = false;
-          if (gram_done < kFusedWaves) {
-            const int s_end = (((c + 1) * kFusedWaves) / nch) & ~(kGramStep - 1);
-            gram_slots(pbt, gram_done, s_end);
-            gram_done = s_end;
-          }
-          DOL_WAVE_FENCE();
-          if constexpr (!RG) cb ^= 1;
-        }
-        if (wave >= 4) __builtin_amdgcn_s_setprio(0);
-        // the k-th and (k+1)-th keys: a wave-uniform branch on k, so that no
-        // per-position predicate on k stays live (in registers) across the loop
-        // (opaque: a comparison per position hoisted out of the unit loop takes
-        // two SGPRs each, which spilled)
-        int ks_ = k;
-        asm volatile("" : "+s"(ks_));
-        int sk, sk1;
-        switch (ks_) {
-          case 1: sk = top[0]; sk1 = top[1]; break;
-          case 2: sk = top[1]; sk1 = top[2]; break;
-          case 3: sk = top[2]; sk1 = top[3]; break;
-          case 4: sk = top[3]; sk1 = top[4]; break;
-          case 5: sk = top[4]; sk1 = top[5]; break;
-          case 6: sk = top[5]; sk1 = top[6]; break;
-          case 7: sk = top[6]; sk1 = top[7]; break;
-          default: sk = top[7]; sk1 = rej; break;
+          break;
         }
         bool ok = top[0] < kCompPosInf;
         bool nonpos = false;
