@@ -1585,6 +1585,15 @@ hipError_t launch_one(const SegTable& tab, const PathArgs& a, bool fast, Sched s
   const int64_t units = tab.tile_start[tab.nseg];
   int64_t blocks = std::min<int64_t>((int64_t)di.cu_count * occ, units);
   blocks = std::max<int64_t>(blocks, 1);
+  // With a unit per block, the blocks of one layer all add into the same counters
+  // at the same moment.  Where a unit is short (up to 8 experts) or the counters
+  // take 32-bit adds (odd E), more than 160 of them cost more than a second unit
+  // in series: one layer of 128,000 tokens, do_fused, 250 blocks and 125: 4 fp32
+  // experts 26.1 and 23.3 us, 53 bf16 36.7 and 32.1; 83,000 tokens, 162 and 81:
+  // 21.5 and 20.9, 29.6 and 28.7; at 130 units or 16 to 32 experts one unit wins.
+  if (GM != kGramNone && blocks == units && blocks > 160 && a.ncopies <= 1 && (a.E <= 8 || (a.E & 1) != 0) &&
+      tab.s[0].layer == tab.s[tab.nseg - 1].layer)
+    blocks = (units + 1) / 2;
   sc = plan_units(units, blocks, sc);
   const int flags = (fast ? 1 : 0) | (sc.lp << 1);
   if (pe.start != nullptr || pe.stop != nullptr)  // caller's timing events bound to this dispatch

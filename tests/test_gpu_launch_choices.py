@@ -1,9 +1,16 @@
-"""Aligned fp32 rows whose next chunk's loads are issued together or spread over
+"""Choices of a launch that follow from how many units a block gets.
+
+Aligned fp32 rows whose next chunk's loads are issued together or spread over
 the ranking, a choice by row length and units per block: 64 layers below and
 above the two lines (2 units per block at 512-byte rows, 16 at 1,024-byte rows
 without a Gram), and row lengths that never spread.
 
-The layers repeat two distinct ones: whole numbers, equal to the oracle's.
+The layers repeat two distinct ones.
+
+One layer on a block per unit or on half as many (up to 8 or odd experts, more
+than 160 units).
+
+Whole numbers only: equal to the oracle's.
 """
 import numpy as np
 import pytest
@@ -44,3 +51,16 @@ def test_spread_loads(dl, orc, syn, E, units, gram):
         if D is not None:
             assert all(torch.equal(D[m], D[l]) for m in range(l, L, 2))
             np.testing.assert_array_equal(D_np(D)[l], orc.hamming(F))
+
+
+@pytest.mark.parametrize("E,dtype", [(3, 0), (8, 1), (53, 1), (255, 0), (64, 1)])
+@pytest.mark.parametrize("units", [160, 161, 250])
+def test_one_layer_blocks(dl, orc, syn, E, dtype, units):
+    N, k = 512 * units - 100, min(E, 4)
+    print(f"[case] one layer E={E} N={N} dtype={dtype}", flush=True)
+    x = syn.normal(E + units, N, E, dtype)
+    bits, D, _ = dl.do_fused(to_dev(x), k, want_bits=True)
+    torch.cuda.synchronize()
+    F = orc.topk_signature(x, k)
+    np.testing.assert_array_equal(bits_np(bits, N)[0], orc.pack(F))
+    np.testing.assert_array_equal(D_np(D)[0], orc.hamming(F))
