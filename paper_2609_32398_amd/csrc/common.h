@@ -119,9 +119,11 @@ bool gram_mfma_enabled();
 // do_set_option: false for an unknown option or a value out of range.
 bool set_option(int opt, int value);
 
+// Zeroes n words at p and nrec 64-bit words at rec in one launch.
+hipError_t launch_clear_words(uint32_t* p, int64_t n, u64* rec, int64_t nrec, hipStream_t s);
+
 // Zeroes the accumulators D [L][E][E] and, when out is given, the records that
 // launch_finalize accumulates into.
-hipError_t launch_clear_words(uint32_t* p, int64_t n, u64* rec, int64_t nrec, hipStream_t s);  // n words, nrec records' words
 hipError_t launch_clear(uint32_t* D, do_loss_result* out, int32_t E, int32_t L, hipStream_t s);
 
 // D holds the co-occurrence counts (upper triangle) and becomes
@@ -158,11 +160,12 @@ hipError_t launch_rem_dispatch(const do_rem_move* replicas, const int32_t* n_rep
                                do_rem_move* routes, int32_t* n_routes, int64_t* queue_out, int64_t* tokens_out,
                                hipStream_t s);
 
-// Loss of arbitrary distance matrices.
-// One layer (E <= 256) over ceil(E/8) blocks; fin: three u64 that are zero
+// The finalize of one layer (E <= 256) over ceil(E/8) blocks; fin: three u64 that are zero
 // before the call and zero again after it (cacc must not alias D).
 hipError_t launch_finalize_split(const uint32_t* cacc, uint32_t* D, do_loss_result* out, int32_t E, u64* fin,
                                  hipStream_t s);
+
+// Loss of arbitrary distance matrices.
 hipError_t launch_loss(const uint32_t* D, int32_t E, int32_t L, do_loss_result* out, hipStream_t s);
 
 // The stream's finalize (one layer, E <= 256): the co-occurrence counts are

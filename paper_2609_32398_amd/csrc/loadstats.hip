@@ -260,7 +260,8 @@ hipError_t launch_load_stats(const u64* bits, int64_t N, int64_t ld, int32_t E, 
                              do_dtype dt, const RankMap& rm, uint32_t* loads, do_load_stats_result* out,
                              hipStream_t s) {
   const int64_t W = (N + 63) / 64;
-  // one launch for both (48 layers x 65,536 tokens, 128 bf16 experts: the whole call 144.3 -> 143.0 us)
+  // one launch for both (48 layers x 65,536 tokens, 128 bf16 experts, the whole call: 144 us with two and
+  // 142 to 143 with one, about what runs of one build differ by)
   hipError_t e = launch_clear_words(loads, (int64_t)L * E, reinterpret_cast<u64*>(out),
                                     (int64_t)L * (sizeof(do_load_stats_result) / 8), s);
   if (e != hipSuccess) return e;

@@ -202,11 +202,11 @@ Sched tuned_schedule(do_dtype dt, const SegTable& tab, const PathArgs& a, RowMod
 }
 
 // ---------------------------------------------------------------------------
-// Gram of stored signatures (do_pairwise_hamming; which sizes: launch_gram_mfma)
-// on the same fp4 MFMA tiles as k_topk.  Block b takes layer b / bpl and the part b % bpl of
+// Gram of stored signatures of 97 to 256 experts (which of them:
+// launch_gram_mfma) on the same fp4 MFMA tiles as k_topk.  Block b takes layer b / bpl and the part b % bpl of
 // that layer's 8-word chunks, kGramGroup chunks per step.  A chunk's words of
 // every expert are staged in LDS in the bit-tile layout of k_topk (word s of
-// expert e at s * EPW + (e ^ bt_swz(s))); the next step's words are loaded
+// expert e at s * EP + (e ^ bt_swz(s))); the next step's words are loaded
 // into registers while the current step is multiplied, so one barrier and one
 // memory round trip cover kGramGroup chunks.  Each block adds its counts into
 // cacc at the end; its chunk count stays below 2^24 / 512 (exact fp32 counts).
@@ -217,10 +217,9 @@ constexpr int kGramGroup = 4;  // chunks per step
 template <int EP>
 __global__ __launch_bounds__(kFusedThreads) void k_gram_mfma(const u64* bits, int64_t W, int E, int L, int bpl,
                                                              uint32_t* cacc, bool pair64) {
-  constexpr int EPW = EP < 32 ? 32 : EP;
-  constexpr int kTileWords = EPW * kFusedWaves;
-  constexpr int kPer = (kTileWords + kFusedThreads - 1) / kFusedThreads;  // words per thread and chunk (1..4)
-  typedef GramShape<EPW> GS;
+  constexpr int kTileWords = EP * kFusedWaves;
+  constexpr int kPer = kTileWords / kFusedThreads;  // words per thread and chunk: 2 or 4
+  typedef GramShape<EP> GS;
   typedef typename Mfma<GS::TS>::Acc Acc;
   __shared__ __align__(16) u64 bt[2][kGramGroup][kTileWords];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -248,7 +247,7 @@ __global__ __launch_bounds__(kFusedThreads) void k_gram_mfma(const u64* bits, in
       for (int q = 0; q < kPer; ++q) {
         const int idx = tid + q * kFusedThreads, e = idx >> 3;
         const int64_t w = (g0 + g) * kFusedWaves + (idx & 7);
-        r[g][q] = (idx < kTileWords && g0 + g < c1 && e < E && w < W)
+        r[g][q] = (g0 + g < c1 && e < E && w < W)
                       ? __builtin_nontemporal_load(lb + sig_off(w, e, E))
                       : 0ull;
       }
@@ -261,14 +260,14 @@ __global__ __launch_bounds__(kFusedThreads) void k_gram_mfma(const u64* bits, in
 #pragma unroll
       for (int q = 0; q < kPer; ++q) {
         const int idx = tid + q * kFusedThreads, e = idx >> 3, sl = idx & 7;
-        if (idx < kTileWords) bt[buf][g][sl * EPW + (e ^ bt_swz(sl))] = r[g][q];
+        bt[buf][g][sl * EP + (e ^ bt_swz(sl))] = r[g][q];
       }
     // the tiles are complete; every wave is done with the tiles written two
     // steps ago (it multiplied those before reaching this barrier)
     __syncthreads();
     if (g0 + kGramGroup < c1) load(g0 + kGramGroup);
     const int ng = (int)min((int64_t)kGramGroup, c1 - g0);
-    for (int g = 0; g < ng; ++g) mfma_slots<GS::TS>(acc, wt, bt[buf][g], EPW, 0, kFusedWaves, lane);
+    for (int g = 0; g < ng; ++g) mfma_slots<GS::TS>(acc, wt, bt[buf][g], EP, 0, kFusedWaves, lane);
     buf ^= 1;
   }
   mfma_flush<GS::TS>(acc, wt, cacc + (int64_t)l * E * E, E, lane, (int)(blockIdx.x % kGP), pair64);

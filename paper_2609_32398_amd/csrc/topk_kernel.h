@@ -24,11 +24,14 @@
 // an order-preserving integer (exact for all non-NaN values except that -0
 // sorts one step below +0).  A wave starts with positive keys and switches to
 // general keys for the rest of its tiles after meeting a non-positive
-// threshold.  bf16 keys keep all 16 value bits; fp32 keys keep 24, so a token
+// threshold; a bf16 row goes back to positive keys once the 8th key of every
+// token of the wave is positive.  bf16 keys keep all 16 value bits; fp32 keys keep 24, so a token
 // whose k-th and (k+1)-th keys share a 24-bit bucket is settled by the whole
-// wave from the full values of that bucket.  A token whose threshold lands on
-// +-0, +-inf or NaN, or is not positive under positive keys, is re-ranked by
-// an exact per-lane fallback on 64-bit keys.
+// wave from the full values of that bucket.  A row whose threshold is not
+// positive under positive keys is ranked once more with general keys where its
+// scores are still in LDS (one chunk, bf16) or are cheap to load again
+// (kRagged); else, and where the threshold lands on +-0, +-inf or NaN, the token
+// is re-ranked by an exact per-lane fallback on 64-bit keys.
 //
 // Gram.  Default: scaled fp4 (e2m1) MFMA, v_mfma_scale_f32_32x32x64_f8f6f4 at
 // 256 experts and v_mfma_scale_f32_16x16x128_f8f6f4 below, on operands
@@ -1284,7 +1287,7 @@ __global__ __launch_bounds__(kFusedThreads) void k_topk(const SegTable tab_arg, 
   // meeting a non-positive threshold.  bf16 rows and fp32 rows of one chunk look
   // at it after the first chunk and rank that again from LDS (8 fp32 experts,
   // 4,096 tokens, where nearly every wave meets one: 21.5 -> 16.4 us); longer fp32 rows
-  // look at their end, and those tokens are re-ranked exactly.
+  // look at their end, and those tokens are re-ranked exactly (kRagged: the row again).
   bool gen = false;
   // only these rows can be ranked again after their first chunk
   constexpr bool kRankAgain = Traits<T>::kExact || EP == 32;
@@ -1396,8 +1399,9 @@ __global__ __launch_bounds__(kFusedThreads) void k_topk(const SegTable tab_arg, 
             DOL_WAVE_FENCE();
             unsigned char* other = st + (cb ^ 1) * kChunkBytes;
             // `spread`: the eight loads of the next chunk are issued one after each
-            // ranked piece.  Issued together they queued behind those of the other
-            // waves and held up waves 4-7 for 18 % of their time.  After the block's
+            // ranked piece.  Issued together they queue behind those of the other
+            // waves (a build with clock reads around them, 48 layers x 262,144 bf16
+            // tokens, 128 experts: 18 % of the time of waves 4-7).  After the block's
             // last chunk they read the current chunk once more, into a free buffer.
             const unsigned char* nrow = word_rows(sv, wl, rowB) + (c + 1 < nch ? c + 1 : c) * 128;
             if (c + 1 == nch && next_mine) nrow = word_rows(svn, wln, rowB);
