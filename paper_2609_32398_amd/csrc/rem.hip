@@ -299,6 +299,7 @@ __device__ __forceinline__ int dispatch_passes(V* T, V* Q, u64* order, const uin
   const V tf = (V)(total / R), tc = (V)((total + R - 1) / R);
   int n = 0;
   for (int d = 0; d < D; ++d) {
+    const int before = n;
     // ranks by queue depth, ties by index: position = number of smaller keys
     for (int r = lane; r < R; r += kWave) {
       const V q = Q[r];
@@ -361,6 +362,7 @@ __device__ __forceinline__ int dispatch_passes(V* T, V* Q, u64* order, const uin
       }
       lds_order();
     }
+    if (n == before) break;  // nothing moved: every later pass would see the same
   }
   return n;
 }
@@ -380,6 +382,7 @@ __device__ __forceinline__ int dispatch_rounds(V* T, V* Q, u64* order, const uin
   const V tf = (V)(total / R), tc = (V)((total + R - 1) / R);
   int n = 0;
   for (int d = 0; d < D; ++d) {
+    const int before = n;
     if (lane < R) {
       const V q = Q[lane];
       int pos = 0;
@@ -441,6 +444,7 @@ __device__ __forceinline__ int dispatch_rounds(V* T, V* Q, u64* order, const uin
       open = j < 63 ? ~0ull << (j + 1) : 0ull;
       lds_order();
     }
+    if (n == before) break;  // nothing moved: every later pass would see the same
     lds_order();
   }
   return n;

@@ -84,3 +84,19 @@ def test_many_replicas_on_one_rank(dl):
     torch.cuda.synchronize()
     want, Q, _ = rem.dispatch([(a, b, c) for a, b, c, _ in reps], T, home, R, D)
     assert dl.rem_records(r, nr)[0] == want and qo[0].tolist() == Q
+
+
+@pytest.mark.parametrize("E,R,D", [(8, 1, 50), (12, 3, 60), (40, 5, 17), (140, 70, 30)])
+def test_more_passes_than_routes(dl, E, R, D):
+    """The dispatch ends with the first pass that routes nothing: the passes after it would change nothing."""
+    rng = random.Random(E + D)
+    home = [e % R for e in range(E)]
+    reps = [(e, home[e], rng.randrange(R)) for e in range(E) for _ in range(3)]
+    rec = [[a | (b << 32), c, 0] for a, b, c in reps]
+    T = [rng.randrange(1000) * (1 + 9 * (home[e] == 0)) for e in range(E)]
+    r, nr, qo, t1 = dl.do_rem_dispatch(_dev([rec]), torch.tensor([len(rec)], dtype=torch.int32, device="cuda"),
+                                       _dev([T]), home, R, D)
+    torch.cuda.synchronize()
+    want, Q, left = rem.dispatch(reps, T, home, R, D)
+    assert len(want) < R * D
+    assert dl.rem_records(r, nr)[0] == want and qo[0].tolist() == Q and t1[0].tolist() == left
