@@ -216,37 +216,44 @@ __global__ __launch_bounds__(kWideThreads) void k_topk_wide(const SegTable tab_a
       int rej = INT_MIN;
 #pragma unroll
       for (int i = 0; i < KL; ++i) top[i] = INT_MIN;
-      for (int c = 0; c < nch; ++c) {
+      int sk, sk1;
+      // fp32: a row whose threshold is not positive is loaded and ranked once more
+      // with general keys, which the wave then keeps (569 experts, 5 x 56 negative
+      // tokens: 149 us with the exact per-lane selection after the first ranking,
+      // 55 this way)
+      for (;;) {
+        for (int c = 0; c < nch; ++c) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) *reinterpret_cast<v4u*>(st + j * 1024 + lane * 16) = pre[j];
-        DOL_WAVE_FENCE();
-        if (c + 1 < nch)
-          fetch(sv, wl, c + 1);
-        else if (next_mine)
-          fetch(svn, tl0n + wave, 0);
-        const int nv = (min(128, rowB - 128 * c) + 15) >> 4;
-        const int tail_q = dup != 0 && c + 1 == nch ? nv - 1 : -1;
-        const int e0 = c * 8 * Traits<T>::kVec;
-        if (gen)
-          rank_wide<T, KL, true>(st, lane, e0, nv, tail_q, dup, E, vmask, sel_lo, sel_hi, top, rej);
-        else
-          rank_wide<T, KL, false>(st, lane, e0, nv, tail_q, dup, E, vmask, sel_lo, sel_hi, top, rej);
-        DOL_WAVE_FENCE();
-      }
-      int sk = top[0], sk1 = rej;
+          for (int j = 0; j < 8; ++j) *reinterpret_cast<v4u*>(st + j * 1024 + lane * 16) = pre[j];
+          DOL_WAVE_FENCE();
+          if (c + 1 < nch)
+            fetch(sv, wl, c + 1);
+          else if (next_mine)
+            fetch(svn, tl0n + wave, 0);
+          const int nv = (min(128, rowB - 128 * c) + 15) >> 4;
+          const int tail_q = dup != 0 && c + 1 == nch ? nv - 1 : -1;
+          const int e0 = c * 8 * Traits<T>::kVec;
+          if (gen)
+            rank_wide<T, KL, true>(st, lane, e0, nv, tail_q, dup, E, vmask, sel_lo, sel_hi, top, rej);
+          else
+            rank_wide<T, KL, false>(st, lane, e0, nv, tail_q, dup, E, vmask, sel_lo, sel_hi, top, rej);
+          DOL_WAVE_FENCE();
+        }
+        sk = top[0], sk1 = rej;
 #pragma unroll
-      for (int i = 0; i < KL; ++i) {
-        sk = i == k - 1 ? top[i] : sk;
-        sk1 = i == k ? top[i] : sk1;
+        for (int i = 0; i < KL; ++i) {
+          sk = i == k - 1 ? top[i] : sk;
+          sk1 = i == k ? top[i] : sk1;
+        }
+        if (Traits<T>::kExact || gen || __ballot(valid && sk < WideKey<T>::kPosMin) == 0ull) break;
+        gen = true;
+        rej = INT_MIN;
+#pragma unroll
+        for (int i = 0; i < KL; ++i) top[i] = INT_MIN;
+        fetch(sv, wl, 0);
       }
       bool ok = top[0] < kCompPosInf;
-      bool nonpos = false;
-      if (gen) {
-        ok = ok && sk > kCompNegInfMax && (sk < WideKey<T>::kZeroLo || sk > WideKey<T>::kZeroHi);
-      } else {
-        nonpos = valid && sk < WideKey<T>::kPosMin;
-        ok = ok && !nonpos;
-      }
+      if (gen) ok = ok && sk > kCompNegInfMax && (sk < WideKey<T>::kZeroLo || sk > WideKey<T>::kZeroHi);
       const bool tie = !Traits<T>::kExact && valid && ok && ((sk1 >> 10) == (sk >> 10));
       // the k selected entries are top[0..k); a lane or a tied entry that
       // selects nothing ORs a zero (no divergent branches, as in k_topk)
@@ -263,7 +270,6 @@ __global__ __launch_bounds__(kWideThreads) void k_topk_wide(const SegTable tab_a
         const u64 tm = __ballot(tie);
         if (tm != 0ull) resolve_ties_wide(tm, sk, need, gen, mybt, word_rows(sv, wl, rowB), E, swz);
       }
-      if (__ballot(nonpos) != 0ull) gen = true;
       const bool slow = valid && !ok;
       if (__ballot(slow) != 0ull) {
         const T* rp = reinterpret_cast<const T*>(word_rows(sv, wl, rowB) + (uint32_t)lane * (uint32_t)rowB);
