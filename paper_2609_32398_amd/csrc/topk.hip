@@ -524,9 +524,14 @@ hipError_t launch_topk(do_dtype dt, SegTable& tab, int nseg, const PathArgs& a, 
   // 32 partitions: 16 layers x 65,536 tokens 90 / 74 / 74, 32 x 65,536 164 / 134 /
   // 121, 48 x 16,384 76.5 / 74.7 / 73.9, 48 x 262,144 685 / 653 / 636.  Below 16
   // layers the choice is not clear: 8 layers x 262,144 take 150 / 125 / 129 in
-  // bf16 and 193 / 198 / 202 in fp32.
+  // bf16 and 193 / 198 / 202 in fp32.  Below four units per CU a block's share is
+  // one range; small partitions that it does not divide move those ranges off the
+  // layers' ends (36 layers x 3,762: 36.1 / 36.4 / 41.3, in fp32 41.5 / 41.5 /
+  // 46.3), even ones gain a little (48 x 8,192: 49.3 / 48.5 / 48.4).
   const int layers = tab.s[nseg - 1].layer - tab.s[0].layer + 1;
-  if (sc.lp == 3 && a.cacc != nullptr) sc.lp = layers >= 32 ? 5 : layers >= 16 ? 4 : 3;
+  const int64_t units = tab.tile_start[nseg], cus = device_info().cu_count;
+  if (sc.lp == 3 && a.cacc != nullptr && (units >= 4 * cus || units % cus == 0))
+    sc.lp = layers >= 32 ? 5 : layers >= 16 ? 4 : 3;
   // a tuner trial binds its events to the dispatch (the kernel alone), unless
   // the caller's timing events already are; then they go around the launch
   ProfEv use = pe;
