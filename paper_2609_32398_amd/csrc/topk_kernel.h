@@ -54,6 +54,8 @@
 
 namespace dol {
 
+constexpr int kWideMaxK = 16;  // longest list of a per-lane selection; above: one pass per pick
+
 namespace {
 
 typedef uint32_t v4u __attribute__((ext_vector_type(4)));
@@ -1597,6 +1599,10 @@ hipError_t launch_one(const SegTable& tab, const PathArgs& a, bool fast, Sched s
   if (e != hipSuccess) return e;
   int occ = 1;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kern, kFusedThreads, lds) != hipSuccess || occ < 1) occ = 1;
+  // the k passes of the per-lane selection read their rows k times: a second
+  // block's rows push the first's out of the caches (2 layers x 112,633 tokens of
+  // 483 experts, k = 21: bf16 12.7 ms, 10.5 with one block per CU, fp32 16.8, 11.8)
+  if (!fast && a.k > kWideMaxK) occ = 1;
   const DevInfo di = device_info();
   const int64_t units = tab.tile_start[tab.nseg];
   int64_t blocks = std::min<int64_t>((int64_t)di.cu_count * occ, units);
@@ -1631,7 +1637,6 @@ hipError_t launch_mode(int gm, const SegTable& tab, const PathArgs& a, bool fast
 }  // namespace
 
 // More than 256 experts and k <= kWideMaxK, signatures only (topk_wide.hip).
-constexpr int kWideMaxK = 16;
 hipError_t launch_wide(do_dtype dt, const SegTable& tab, const PathArgs& a, hipStream_t s, const ProfEv& pe);
 
 // The launches of the kPieces rows (topk_pieces.hip).
