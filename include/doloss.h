@@ -33,8 +33,10 @@
  *                        significant bit first); bits past N in word
  *                        ceil(N/64) - 1 are zero.  A layer is E * Wp words,
  *                        Wp = 8 * U ("padded words per expert"); the words
- *                        past ceil(N/64) of the last unit are neither written
- *                        nor read.  One unit of every expert is 64 * E
+ *                        past ceil(N/64) of the last unit are written as
+ *                        zeros by calls on whole layers, left as they are by
+ *                        stream appends, and their values never matter where
+ *                        signatures are read.  One unit of every expert is 64 * E
  *                        contiguous bytes, which the Top-K kernel writes at
  *                        once (Sec. 3.1.1 defines F_i as N bits per expert;
  *                        the tiling is this library's).
@@ -368,8 +370,8 @@ do_status do_rem_dispatch(const do_rem_move* replicas, const int32_t* n_replicas
  *                        and keeps the faster; 0 fixes the XCD-partitioned
  *                        schedule; 1 fixes one contiguous range of work units
  *                        per block.
- *   DO_OPT_GRAM          co-occurrence Gram for E <= 256: 0 (default) the fp4
- *                        MFMA Gram, 1 the VALU popcount Gram.
+ *   DO_OPT_GRAM          co-occurrence Gram: 0 (default) the fp4 MFMA Gram, 1
+ *                        the VALU popcount Gram.
  * The third adds an input check.  NaN scores have a defined rank (below -inf,
  * equal to each other), so results are defined without it:
  *   DO_OPT_CHECK_FINITE  0 (default) off; 1: do_topk_signature, do_fused,
